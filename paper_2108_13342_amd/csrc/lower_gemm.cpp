@@ -619,6 +619,25 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = MFMA(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
+#elif BK % (8 * WAVES_K) == 0
+    // The order of K is free as long as both operands keep it: a lane takes four consecutive K values of its row in one
+    // 16-byte read and feeds them to four instructions (the lower half of the wavefront K 0..3, the upper half 4..7 of a
+    // group of eight), a quarter of the LDS instructions of one 4-byte read per operand and matrix instruction.
+#pragma unroll
+    for (int kq = 0; kq < BK / 8 / WAVES_K; ++kq) {
+      f32x4 fa[TM], fb[TN];
+      const int kcol = (kq * WAVES_K + wk) * 8 + (lane >> 5) * 4;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[i] = *(const f32x4*)&As[buf][wm * WTM + i * 32 + (lane & 31)][kcol];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[j] = *(const f32x4*)&Bs[buf][wn * WTN + j * 32 + (lane & 31)][kcol];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+    }
 #else
 #pragma unroll
     for (int kq = 0; kq < BK / 2 / WAVES_K; ++kq) {
@@ -1235,9 +1254,28 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
       if (cost(cands[i]) < cost(cands[pick])) pick = (int)i;
   }
   Cfg f = cands[pick];
-  // a problem too small to occupy the chip with 64x64 tiles: 32x32 tiles, the four wavefronts of a
-  // workgroup splitting K between them
-  if (c.opts.force_variant < 100 && nblocks(64, 64) < 192 && K >= 8 * BK0) f = {32, 32, BK0, 1, 1, 4, 1, 2};
+  // A problem too small to occupy the chip with 64x64 tiles: 32x32 tiles whose wavefronts split K between them.  One
+  // or two such workgroups per compute unit hide little from each other, so the kernel is the chain of its K tiles - a
+  // memory round trip and two barriers each - and long tiles on eight wavefronts shorten it.  Product + bias, us, four
+  // wavefronts on the short tile (K 64 in 16 bits, 16 in f32) against this form (M x K x N): bf16 33x3072x768
+  // 21.3 -> 14.3, 77x3072x768 18.4 -> 12.2, 33x768x3072 8.5 -> 7.5, 33x768x768 4.4 -> 4.3; f32 256x3072x768 62.0 ->
+  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Lengths: 16-bit 384 (512 is 0.3-0.5 us slower), 256
+  // where a compute unit holds several workgroups (500x768x768: 5.2, with 384 5.5); f32 128 (256 is 0.3-1.2 us slower);
+  // of these the one that pads K least.  Where the line lies: f32 up to one round of 64x64 tiles (256x768x3072, 192
+  // tiles: 29.9 -> 22.8, 1200x768x768, 228 tiles: 23.0 -> 20.3), 16-bit products of a K below 512 up to 96 tiles
+  // (against 64x64 tiles 200x384x1536: 4.9 -> 4.1, 300x256x768: 4.0 -> 3.2).  Operands read element by element keep
+  // the short tile: a long one would not fit their registers.
+  const bool vec_loads = amode != 2 && bmode != 2;
+  const int64_t n64 = nblocks(64, 64);
+  if (c.opts.force_variant < 100 && ((n64 < 192 && K >= 8 * BK0) || (vec_loads && (eb == 2 ? n64 <= 96 && K >= 256 : n64 <= 256 && K >= 128)))) {
+    f = {32, 32, BK0, 1, 1, 4, 1, 2};
+    const int step = eb == 2 ? 128 : 64;             // one matrix step (16-bit) or 16-byte fragment (f32) of each of eight wavefronts
+    int64_t least = -1;
+    for (int bk = (eb == 2 && nblocks(32, 32) <= 256 ? 3 : 2) * step; bk >= step && vec_loads; bk -= step) {
+      const int64_t pad = (K + bk - 1) / bk * bk - K;
+      if (least < 0 || pad < least) { least = pad; f = {32, 32, bk, 1, 1, 8, 1, 2}; }
+    }
+  }
   int BM = f.BM, BN = f.BN, BK = f.BK, WAVES_M = f.WM, WAVES_N = f.WN, WAVES_K = f.WK, NBUF = f.NBUF, PF = f.PF, DMA = f.DMA;
   // developer override for tuning runs: DNNF_GEMM_TILE=BM,BN,BK,WAVES_M,WAVES_N,NBUF[,PF[,DMA[,MIN_N]]]
   if (const char* ov = getenv("DNNF_GEMM_TILE")) {

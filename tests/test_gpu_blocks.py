@@ -82,6 +82,24 @@ def test_gemm_tile_configurations(tile, monkeypatch):
     assert [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2][0].startswith(f"mfma_{bm}x{bn}x64")
 
 
+@pytest.mark.parametrize("M,K,N,dtype,kw,tile", [
+    (33, 768, 520, "bf16", dict(residual=True, w_transposed=True), "32x32x384_a0b0_w8"),      # whole K tiles, a row in the second tile
+    (1, 3072, 77, "f16", dict(w_transposed=True), "32x32x384_a0b0_w8"),                       # one row, columns of odd number
+    (65, 520, 96, "f16", dict(gelu=True), "32x32x"),                                          # K ends inside a tile
+    (70, 384, 40, "bf16", dict(), "32x32x384"),                                               # a single K tile
+    (31, 512, 33, "bf16", dict(bias=False, w_transposed=True), "32x32x256_a0b0_w8"),          # two K tiles
+    (40, 256, 2624, "f32", dict(residual=True), "32x32x128"),                                 # f32: 16-byte fragments
+    (33, 132, 68, "f32", dict(w_transposed=True), "32x32x"),                                  # f32, the smallest K, ending inside a tile
+    (600, 768, 1000, "f32", dict(gelu=True), "32x32x128"),                                    # more than two workgroups per compute unit
+    (40, 513, 60, "f16", dict(), "32x32x64_"),                                                # element loaders keep short tiles
+])
+def test_gemm_long_k_tiles(M, K, N, dtype, kw, tile):
+    """Products of few tiles: eight wavefronts split long K tiles."""
+    s, _ = check_against_oracle(U.gemm_block(M, K, N, dtype, **kw))
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
+    assert names[0].startswith("mfma_" + tile), names
+
+
 @pytest.mark.parametrize("tile", ["64,64,64,2,2,2,1,1", "128,64,64,2,2,2,1,1", "128,128,64,2,2,2,1,1", "256,128,64,4,2,2,1,1", "256,256,64,4,2,2,1,1",
                                   "128,128,64,2,4,2,1,1", "64,128,64,2,4,2,1,1", "128,64,64,4,2,2,1,1", "256,256,64,4,4,2,1,1"])
 @pytest.mark.parametrize("dtype,N", [("bf16", 520), ("f16", 520), ("bf16", 777)])

@@ -1259,21 +1259,32 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   // memory round trip and two barriers each - and long tiles on eight wavefronts shorten it.  Product + bias, us, four
   // wavefronts on the short tile (K 64 in 16 bits, 16 in f32) against this form (M x K x N): bf16 33x3072x768
   // 21.3 -> 14.3, 77x3072x768 18.4 -> 12.2, 33x768x3072 8.5 -> 7.5, 33x768x768 4.4 -> 4.3; f32 256x3072x768 62.0 ->
-  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Lengths: 16-bit 384 (512 is 0.3-0.5 us slower), 256
-  // where a compute unit holds several workgroups (500x768x768: 5.2, with 384 5.5); f32 128 (256 is 0.3-1.2 us slower);
-  // of these the one that pads K least.  Where the line lies: f32 up to one round of 64x64 tiles (256x768x3072, 192
-  // tiles: 29.9 -> 22.8, 1200x768x768, 228 tiles: 23.0 -> 20.3), 16-bit products of a K below 512 up to 96 tiles
-  // (against 64x64 tiles 200x384x1536: 4.9 -> 4.1, 300x256x768: 4.0 -> 3.2).  Operands read element by element keep
-  // the short tile: a long one would not fit their registers.
-  const bool vec_loads = amode != 2 && bmode != 2;
-  const int64_t n64 = nblocks(64, 64);
+  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Where the line lies: f32 up to one round of 64x64 tiles
+  // (256x768x3072, 192 tiles: 29.9 -> 22.8, 1200x768x768, 228 tiles: 23.0 -> 20.3), 16-bit products of a K below 512 up
+  // to 96 tiles (against 64x64 tiles 200x384x1536: 4.9 -> 4.1, 300x256x768: 4.0 -> 3.2).  Operands read element by
+  // element keep the short tile: a long one would not fit their registers.
+  const bool vec_loads = amode != 2 && bmode != 2, direct = amode == 0 && bmode == 0;
+  const int64_t n64 = nblocks(64, 64), n32 = nblocks(32, 32);
   if (c.opts.force_variant < 100 && ((n64 < 192 && K >= 8 * BK0) || (vec_loads && (eb == 2 ? n64 <= 96 && K >= 256 : n64 <= 256 && K >= 128)))) {
     f = {32, 32, BK0, 1, 1, 4, 1, 2};
-    const int step = eb == 2 ? 128 : 64;             // one matrix step (16-bit) or 16-byte fragment (f32) of each of eight wavefronts
-    int64_t least = -1;
-    for (int bk = (eb == 2 && nblocks(32, 32) <= 256 ? 3 : 2) * step; bk >= step && vec_loads; bk -= step) {
-      const int64_t pad = (K + bk - 1) / bk * bk - K;
-      if (least < 0 || pad < least) { least = pad; f = {32, 32, bk, 1, 1, 8, 1, 2}; }
+    // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
+    // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile costs what `share` values of K
+    // would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5, 6.8; 33x768x3072 8.7, 8.6, 8.8;
+    // 33x3072x768 17.5, 15.8, 15.6; 40x3080x768 17.9, 16.5, 16.8.  Much between the transposing loads, where few threads own
+    // a block of 8x8 values: A^T B 320x640x640 9.9, 8.7, 6.6; six products 640x640x64 5.8, 5.3, 5.1.  Tiles of 384 leave LDS for
+    // three workgroups on a compute unit, of 256 for four: one that does not hold K in one or two tiles loses as soon as
+    // there are so many (eight products 896x896x64, 448 workgroups: 10.2, 8.8, 11.4; 15 of 768x768x64, 720: 14.6, 10.0, 10.8).
+    // Tiles of 512 in 16 bits and of 192 or 256 in f32 were no faster in any product.
+    if (vec_loads && eb == 4) f = {32, 32, (K + 63) / 64 % 2 ? 64 : 128, 1, 1, 8, 1, 2};
+    else if (vec_loads) {
+      const int share = direct ? 20 : 150;
+      const int64_t n384 = (K + 383) / 384;
+      const bool with_384 = n32 <= 256 || (!direct && n384 <= (n32 <= 512 ? 2 : 1));
+      int64_t least = 0;
+      for (int bk = with_384 ? 384 : 256; bk >= 128; bk -= 128) {
+        const int64_t work = (K + bk - 1) / bk * (bk + share);
+        if (!least || work < least) { least = work; f = {32, 32, bk, 1, 1, 8, 1, 2}; }
+      }
     }
   }
   int BM = f.BM, BN = f.BN, BK = f.BK, WAVES_M = f.WM, WAVES_N = f.WN, WAVES_K = f.WK, NBUF = f.NBUF, PF = f.PF, DMA = f.DMA;

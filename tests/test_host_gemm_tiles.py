@@ -1,0 +1,47 @@
+"""Tile choice of small MatMuls without a device: which form the default rule takes, read from the kernel's name."""
+import numpy as np
+import pytest
+
+from paper_2108_13342_amd import api
+from workloads import configs
+from workloads.graph import GraphBuilder
+
+
+def _kernel(M, K, N, dtype, batch=(), a_transposed=False, weight=True):
+    """Name of the MatMul kernel of x @ w; without `weight` both operands are activations, w contiguous along N."""
+    b = GraphBuilder("gemm_tiles", dtype)
+    zeros = lambda shape: np.zeros(shape, dtype=np.float32)
+    if a_transposed:
+        x = configs._transpose(b, b.input("x", (K, M), zeros((K, M))), (1, 0))
+    else:
+        x = b.input("x", batch + (M, K), zeros(batch + (M, K)))
+    w = (b.weight if weight else b.input)("w", batch + (K, N), zeros(batch + (K, N)))
+    b.mark_output(configs._matmul(b, x, w))
+    spec = b.finish()
+    g, _ = api.graph_from_spec(spec)
+    g.rewrite()
+    plan = api.Plan(g, [1] * len([t for t in spec.tensors.values() if t.kind == "weight"]))
+    return [d["kernel_name"].split(":")[1] for d in plan.describe() if d["family"] == 2 and not d["prepare_only"]][0]
+
+
+@pytest.mark.parametrize("M,K,N,kw,tile", [
+    # a K that no length divides: the number of tiles counts, not the padding alone
+    (40, 3080, 768, {}, "32x32x256_a0b0_w8"),
+    (40, 3136, 768, {}, "32x32x256_a0b0_w8"),
+    (40, 520, 768, {}, "32x32x128_a0b0_w8"),
+    (40, 1000, 768, {}, "32x32x256_a0b0_w8"),
+    (33, 3072, 768, {}, "32x32x384_a0b0_w8"),
+    # transposing loaders: fewer, longer tiles
+    (640, 640, 64, dict(batch=(6,), weight=False), "32x32x384_a0b1_w8"),
+    (320, 640, 640, dict(a_transposed=True, weight=False), "32x32x384_a1b1_w8"),
+    (504, 384, 768, dict(a_transposed=True, weight=False), "32x32x384_a1b1_w8"),
+    (768, 384, 384, dict(a_transposed=True, weight=False), "32x32x384_a1b1_w8"),
+    (896, 896, 64, dict(batch=(8,), weight=False), "32x32x256_a0b1_w8"),
+])
+def test_length_of_k_tiles_16_bit(M, K, N, kw, tile):
+    assert _kernel(M, K, N, "bf16", **kw) == "mfma_" + tile
+
+
+@pytest.mark.parametrize("K,bk", [(128, 128), (132, 64), (192, 64), (256, 128), (576, 64), (1000, 128), (3080, 64)])
+def test_length_of_k_tiles_f32(K, bk):
+    assert _kernel(256, K, 768, "f32") == f"mfma_32x32x{bk}_a0b0_w8"

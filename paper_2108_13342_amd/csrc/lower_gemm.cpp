@@ -1267,16 +1267,26 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   const int64_t n64 = nblocks(64, 64), n32 = nblocks(32, 32);
   if (c.opts.force_variant < 100 && ((n64 < 192 && K >= 8 * BK0) || (vec_loads && (eb == 2 ? n64 <= 96 && K >= 256 : n64 <= 256 && K >= 128)))) {
     f = {32, 32, BK0, 1, 1, 4, 1, 2};
+    // 16 bits, direct loads, more than one workgroup per compute unit: the workgroups hide each other's round trips, and
+    // short tiles leave room for more of them.  Short against long tiles, us in a loop and (in brackets) in a row of
+    // products whose weights come from beyond the L2 caches: 500x768x768 4.6 (5.9), 4.9 (6.1); 600x768x768 4.7 (5.9), 4.9
+    // (6.0); 900x512x768 4.6 (5.6), 5.1 (5.8); 900x768x768 5.6 (6.9), 6.1 (7.0); 400x384x768 3.6 (4.2), 3.8 (4.5).  Long
+    // tiles where K is long (500x1536x768: 6.8 (9.0), 6.9 (8.9); 600x1536x768: 6.9 (10.2), 6.9 (9.0); 900x3072x768:
+    // 18.2 (19.9), 17.6 (19.1)) or the right operand larger than an L2 cache of 4 MB (128x768x3072: 8.5 (9.9), 8.1 (9.6);
+    // 96x1024x4096: 14.1 (15.2), 13.2 (14.2)); between 2 and 4 MB it is one way in a loop and the other in a row
+    // (300x768x2304: 6.3 (9.1), 6.7 (8.8)).
+    const bool long_16 = !direct || n32 <= 256 || K >= 1536 || (K >= 512 && GZ * GN * K * eb > (4 << 20));
     // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
-    // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile costs what `share` values of K
-    // would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5, 6.8; 33x768x3072 8.7, 8.6, 8.8;
-    // 33x3072x768 17.5, 15.8, 15.6; 40x3080x768 17.9, 16.5, 16.8.  Much between the transposing loads, where few threads own
-    // a block of 8x8 values: A^T B 320x640x640 9.9, 8.7, 6.6; six products 640x640x64 5.8, 5.3, 5.1.  Tiles of 384 leave LDS for
-    // three workgroups on a compute unit, of 256 for four: one that does not hold K in one or two tiles loses as soon as
-    // there are so many (eight products 896x896x64, 448 workgroups: 10.2, 8.8, 11.4; 15 of 768x768x64, 720: 14.6, 10.0, 10.8).
-    // Tiles of 512 in 16 bits and of 192 or 256 in f32 were no faster in any product.
+    // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile
+    // costs what `share` values of K would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5,
+    // 6.8; 33x768x3072 8.7, 8.6, 8.8; 33x3072x768 17.5, 15.8, 15.6; 40x3080x768 17.9, 16.5, 16.8.  Much between the
+    // transposing loads, where few threads own a block of 8x8 values: A^T B 320x640x640 9.9, 8.7, 6.6; six products
+    // 640x640x64 5.8, 5.3, 5.1.  Tiles of 384 leave LDS for three workgroups on a compute unit, of 256 for four: one that
+    // does not hold K in one or two tiles loses as soon as there are so many (eight products 896x896x64, 448 workgroups:
+    // 10.2, 8.8, 11.4; 15 of 768x768x64, 720: 14.6, 10.0, 10.8).  Tiles of 512 in 16 bits and of 192 or 256 in f32 were no
+    // faster in any product.
     if (vec_loads && eb == 4) f = {32, 32, (K + 63) / 64 % 2 ? 64 : 128, 1, 1, 8, 1, 2};
-    else if (vec_loads) {
+    else if (vec_loads && long_16) {
       const int share = direct ? 20 : 150;
       const int64_t n384 = (K + 383) / 384;
       const bool with_384 = n32 <= 256 || (!direct && n384 <= (n32 <= 512 ? 2 : 1));

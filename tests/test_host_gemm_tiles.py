@@ -45,3 +45,24 @@ def test_length_of_k_tiles_16_bit(M, K, N, kw, tile):
 @pytest.mark.parametrize("K,bk", [(128, 128), (132, 64), (192, 64), (256, 128), (576, 64), (1000, 128), (3080, 64)])
 def test_length_of_k_tiles_f32(K, bk):
     assert _kernel(256, K, 768, "f32") == f"mfma_32x32x{bk}_a0b0_w8"
+
+
+@pytest.mark.parametrize("M,K,N,kw,tile", [
+    # more than one 32x32 tile per compute unit, both operands read along K: short tiles ...
+    (500, 768, 768, {}, "32x32x64_a0b0"),
+    (900, 512, 768, {}, "32x32x64_a0b0"),
+    (900, 768, 768, {}, "32x32x64_a0b0"),
+    (400, 384, 768, {}, "32x32x64_a0b0"),
+    (300, 768, 2304, {}, "32x32x64_a0b0"),
+    # ... unless K is long, the weight larger than an L2 cache, or the chip not full
+    (900, 1528, 768, {}, "32x32x64_a0b0"),
+    (900, 1536, 768, {}, "32x32x256_a0b0_w8"),
+    (128, 512, 4096, {}, "32x32x64_a0b0"),
+    (128, 512, 4104, {}, "32x32x256_a0b0_w8"),
+    (128, 768, 3072, {}, "32x32x256_a0b0_w8"),
+    (256, 768, 1024, {}, "32x32x384_a0b0_w8"),
+    (257, 768, 1024, {}, "32x32x64_a0b0"),
+    (512, 512, 64, dict(batch=(12,), weight=False), "32x32x256_a0b1_w8"),
+])
+def test_short_k_tiles_where_workgroups_hide_each_other(M, K, N, kw, tile):
+    assert _kernel(M, K, N, "f16", **kw) == "mfma_" + tile

@@ -1259,13 +1259,22 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   // memory round trip and two barriers each - and long tiles on eight wavefronts shorten it.  Product + bias, us, four
   // wavefronts on the short tile (K 64 in 16 bits, 16 in f32) against this form (M x K x N): bf16 33x3072x768
   // 21.3 -> 14.3, 77x3072x768 18.4 -> 12.2, 33x768x3072 8.5 -> 7.5, 33x768x768 4.4 -> 4.3; f32 256x3072x768 62.0 ->
-  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Where the line lies: f32 up to one round of 64x64 tiles
-  // (256x768x3072, 192 tiles: 29.9 -> 22.8, 1200x768x768, 228 tiles: 23.0 -> 20.3), 16-bit products of a K below 512 up
-  // to 96 tiles (against 64x64 tiles 200x384x1536: 4.9 -> 4.1, 300x256x768: 4.0 -> 3.2).  Operands read element by
-  // element keep the short tile: a long one would not fit their registers.
+  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Operands read element by element keep the short tile: a
+  // long one would not fit their registers.
+  // Where the line lies (64x64 tiles against this form): f32 up to one round of 64x64 tiles (256x768x3072, 192 tiles: 28.3,
+  // 22.2; 1024x3072x1024, 256 tiles: 83.1, 72.6), 16-bit products of a K below 512 up to 96 tiles (200x384x1536: 4.6, 3.7;
+  // 300x256x768: 3.8, 3.0).  A left operand that comes through the transposing loader is turned once for every column of
+  // tiles, so larger tiles win earlier: in 16 bits beyond 128 tiles (128 tiles A^T B 1000x768x512: 12.9, 12.1; 132 tiles
+  // 704x704x768: 12.4, 24.9; 144 tiles 768x512x768: 9.7, 13.0; A^T W 768x512x768: 7.5, 8.0; 180 tiles 904x1024x768: 16.2, 31.1),
+  // in f32 beyond 192 (192 tiles A^T B 1024x512x768: 19.3, 17.8; 195 tiles 960x256x832: 11.2, 12.4; 256 tiles 1024x512x1024:
+  // 19.7, 22.5; A^T W 1024x300x1024: 11.2, 13.5; 900x512x1000: 17.1, 17.8), unless the right one is read along K and K is long
+  // (A^T W 1024x768x1024: 28.1, 25.9).
   const bool vec_loads = amode != 2 && bmode != 2, direct = amode == 0 && bmode == 0;
   const int64_t n64 = nblocks(64, 64), n32 = nblocks(32, 32);
-  if (c.opts.force_variant < 100 && ((n64 < 192 && K >= 8 * BK0) || (vec_loads && (eb == 2 ? n64 <= 96 && K >= 256 : n64 <= 256 && K >= 128)))) {
+  bool split_k = n64 < 192 && K >= 8 * BK0;
+  if (vec_loads && eb == 2) split_k = (K >= 512 && n64 < (amode == 1 ? 129 : 192)) || (K >= 256 && n64 <= 96);
+  else if (vec_loads) split_k = K >= 128 && n64 <= (amode == 1 && (bmode == 1 || K < 768) ? 192 : 256);
+  if (c.opts.force_variant < 100 && split_k) {
     f = {32, 32, BK0, 1, 1, 4, 1, 2};
     // 16 bits, direct loads, more than one workgroup per compute unit: the workgroups hide each other's round trips, and
     // short tiles leave room for more of them.  Short against long tiles, us in a loop and (in brackets) in a row of

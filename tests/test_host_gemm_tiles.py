@@ -66,3 +66,34 @@ def test_length_of_k_tiles_f32(K, bk):
 ])
 def test_short_k_tiles_where_workgroups_hide_each_other(M, K, N, kw, tile):
     assert _kernel(M, K, N, "f16", **kw) == "mfma_" + tile
+
+
+@pytest.mark.parametrize("M,K,N,dtype,weight,tile", [
+    # a transposed left operand: larger tiles from fewer tiles on
+    (1000, 768, 512, "bf16", False, "32x32x384_a1b1_w8"),         # 128 tiles of 64x64
+    (704, 704, 768, "bf16", False, "64x64x64_a1b1"),              # 132
+    (768, 512, 768, "bf16", False, "64x64x64_a1b1"),              # 144
+    (904, 1024, 768, "f16", False, "64x64x64_a1b1"),              # 180
+    (768, 512, 768, "bf16", True, "64x64x64_a1b0"),
+    (904, 768, 768, "bf16", True, "64x64x64_a1b0"),
+    (1024, 512, 768, "f32", False, "32x32x128_a1b1_w8"),          # 192
+    (960, 256, 832, "f32", False, "64x64x16_a1b1"),               # 195
+    (1024, 512, 1024, "f32", False, "64x64x16_a1b1"),             # 256
+    (1024, 768, 1024, "f32", False, "64x64x16_a1b1"),
+    (1024, 300, 1024, "f32", True, "64x64x16_a1b0"),
+    (900, 512, 1000, "f32", True, "64x64x16_a1b0"),               # 240
+    (1024, 768, 1024, "f32", True, "32x32x128_a1b0_w8"),
+])
+def test_line_for_a_transposed_left_operand(M, K, N, dtype, weight, tile):
+    assert _kernel(M, K, N, dtype, a_transposed=True, weight=weight) == "mfma_" + tile
+
+
+@pytest.mark.parametrize("M,K,N,dtype,tile", [
+    (384, 256, 1024, "bf16", "32x32x64_a0b0"), (385, 256, 1024, "bf16", "64x64x64_a0b0_dma"),              # K below 512: 96 tiles, 112 tiles
+    (64, 248, 768, "bf16", "64x64x64_a0b0"), (64, 256, 768, "bf16", "32x32x256_a0b0_w8"),                  # the smallest K in 16 bits
+    (704, 1536, 1024, "f16", "32x32x256_a0b0_w8"), (768, 1536, 1024, "f16", "64x64x64_a0b0_dma"),          # 176 tiles, 192 tiles
+    (1024, 256, 1024, "f32", "32x32x128_a0b0_w8"), (1088, 256, 1024, "f32", "128x64x16_a0b0"),             # 256 tiles, 272 tiles
+    (64, 124, 768, "f32", "64x64x16_a0b0"), (64, 128, 768, "f32", "32x32x128_a0b0_w8"),                    # the smallest K in f32
+])
+def test_lines_between_tile_forms(M, K, N, dtype, tile):
+    assert _kernel(M, K, N, dtype) == "mfma_" + tile

@@ -1274,6 +1274,13 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   bool split_k = n64 < 192 && K >= 8 * BK0;
   if (vec_loads && eb == 2) split_k = (K >= 512 && n64 < (amode == 1 ? 129 : 192)) || (K >= 256 && n64 <= 96);
   else if (vec_loads) split_k = K >= 128 && n64 <= (amode == 1 && (bmode == 1 || K < 768) ? 192 : 256);
+  // f32, direct loads, more than one and a half workgroups per compute unit: the matrix cores are the bound, and zeros
+  // behind K cost what values do.  Where more than a quarter of K would be zeros (K below 205) the short tile on four
+  // wavefronts stays up to 191 tiles (900x132x768: 5.7, 6.0 with 192 values instead of 132; 500x136x900: 4.6, 4.8) and the
+  // 64x64 tile beyond (1024x132x1024: 6.0, 7.0; 1024x200x1024: 7.3, 8.3).
+  const int bk_f32 = (K + 63) / 64 % 2 ? 64 : 128;
+  const bool zeros = eb == 4 && direct && n32 > 384 && ((K + bk_f32 - 1) / bk_f32 * bk_f32 - K) * 4 > K;
+  if (zeros) split_k = n64 < 192 && K >= 128;
   if (c.opts.force_variant < 100 && split_k) {
     f = {32, 32, BK0, 1, 1, 4, 1, 2};
     // 16 bits, direct loads, more than one workgroup per compute unit: the workgroups hide each other's round trips, and
@@ -1294,8 +1301,8 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // does not hold K in one or two tiles loses as soon as there are so many (eight products 896x896x64, 448 workgroups:
     // 10.2, 8.8, 11.4; 15 of 768x768x64, 720: 14.6, 10.0, 10.8).  Tiles of 512 in 16 bits and of 192 or 256 in f32 were no
     // faster in any product.
-    if (vec_loads && eb == 4) f = {32, 32, (K + 63) / 64 % 2 ? 64 : 128, 1, 1, 8, 1, 2};
-    else if (vec_loads && long_16) {
+    if (vec_loads && eb == 4 && !zeros) f = {32, 32, bk_f32, 1, 1, 8, 1, 2};
+    else if (vec_loads && eb == 2 && long_16) {
       const int share = direct ? 20 : 150;
       const int64_t n384 = (K + 383) / 384;
       const bool with_384 = n32 <= 256 || (!direct && n384 <= (n32 <= 512 ? 2 : 1));

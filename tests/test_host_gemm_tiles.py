@@ -97,3 +97,18 @@ def test_line_for_a_transposed_left_operand(M, K, N, dtype, weight, tile):
 ])
 def test_lines_between_tile_forms(M, K, N, dtype, tile):
     assert _kernel(M, K, N, dtype) == "mfma_" + tile
+
+
+@pytest.mark.parametrize("M,K,N,batch,tile", [
+    # long f32 tiles that would be filled up with zeros on a full chip
+    (900, 132, 768, (), "32x32x16_a0b0"),
+    (500, 136, 900, (), "32x32x16_a0b0"),
+    (1024, 132, 1024, (), "64x64x16_a0b0"),
+    (1024, 200, 1024, (), "64x64x16_a0b0"),
+    (256, 132, 768, (), "32x32x64_a0b0_w8"),              # the chip is not full
+    (700, 160, 768, (), "32x32x64_a0b0_w8"),              # few zeros
+    (1024, 256, 1024, (), "32x32x128_a0b0_w8"),
+    (200, 200, 64, (40,), "32x32x128_a0b1_w8"),           # the transposing loader gains all the same
+])
+def test_f32_tiles_filled_with_zeros(M, K, N, batch, tile):
+    assert _kernel(M, K, N, "f32", batch=batch, weight=not batch) == "mfma_" + tile

@@ -1295,7 +1295,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
     // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile
     // costs what `share` values of K would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5,
-    // 6.8; 33x768x3072 8.7, 8.6, 8.8; 33x3072x768 17.5, 15.8, 15.6; 40x3080x768 17.9, 16.5, 16.8.  Much between the
+    // 6.8; 300x1288x768 6.8, 6.9, 7.1; 33x3072x768 17.5, 15.8, 15.6; 40x3080x768 17.9, 16.5, 16.8.  Much between the
     // transposing loads, where few threads own a block of 8x8 values: A^T B 320x640x640 9.9, 8.7, 6.6; six products
     // 640x640x64 5.8, 5.3, 5.1.  Tiles of 384 leave LDS for three workgroups on a compute unit, of 256 for four: one that
     // does not hold K in one or two tiles loses as soon as there are so many (eight products 896x896x64, 448 workgroups:
@@ -1303,7 +1303,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // faster in any product.
     if (vec_loads && eb == 4 && !zeros) f = {32, 32, bk_f32, 1, 1, 8, 1, 2};
     else if (vec_loads && eb == 2 && long_16) {
-      const int share = direct ? 20 : 150;
+      const int share = direct ? 18 : 150;
       const int64_t n384 = (K + 383) / 384;
       const bool with_384 = n32 <= 256 || (!direct && n384 <= (n32 <= 512 ? 2 : 1));
       int64_t least = 0;

@@ -30,6 +30,7 @@ def _kernel(M, K, N, dtype, batch=(), a_transposed=False, weight=True):
     (40, 3136, 768, {}, "32x32x256_a0b0_w8"),
     (40, 520, 768, {}, "32x32x128_a0b0_w8"),
     (40, 1000, 768, {}, "32x32x256_a0b0_w8"),
+    (300, 1288, 768, {}, "32x32x128_a0b0_w8"),
     (33, 3072, 768, {}, "32x32x384_a0b0_w8"),
     # transposing loaders: fewer, longer tiles
     (640, 640, 64, dict(batch=(6,), weight=False), "32x32x384_a0b1_w8"),

@@ -85,11 +85,11 @@ def test_gemm_tile_configurations(tile, monkeypatch):
 @pytest.mark.parametrize("M,K,N,dtype,kw,tile", [
     (33, 768, 520, "bf16", dict(residual=True, w_transposed=True), "32x32x384_a0b0_w8"),      # whole K tiles, a row in the second tile
     (1, 3072, 77, "f16", dict(w_transposed=True), "32x32x384_a0b0_w8"),                       # one row, columns of odd number
-    (65, 520, 96, "f16", dict(gelu=True), "32x32x"),                                          # K ends inside a tile
+    (65, 520, 96, "f16", dict(gelu=True), "32x32x128_a0b0_w8"),                               # K ends inside a tile
     (70, 384, 40, "bf16", dict(), "32x32x384"),                                               # a single K tile
     (31, 512, 33, "bf16", dict(bias=False, w_transposed=True), "32x32x256_a0b0_w8"),          # two K tiles
     (40, 256, 2624, "f32", dict(residual=True), "32x32x128"),                                 # f32: 16-byte fragments
-    (33, 132, 68, "f32", dict(w_transposed=True), "32x32x"),                                  # f32, the smallest K, ending inside a tile
+    (33, 132, 68, "f32", dict(w_transposed=True), "32x32x64_a0b0_w8"),                        # f32, ending inside a tile
     (600, 768, 1000, "f32", dict(gelu=True), "32x32x128"),                                    # more than two workgroups per compute unit
     (40, 513, 60, "f16", dict(), "32x32x64_"),                                                # element loaders keep short tiles
 ])
@@ -98,6 +98,53 @@ def test_gemm_long_k_tiles(M, K, N, dtype, kw, tile):
     s, _ = check_against_oracle(U.gemm_block(M, K, N, dtype, **kw))
     names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
     assert names[0].startswith("mfma_" + tile), names
+
+
+@pytest.mark.parametrize("M,K,N,dtype,kw,tile", [
+    # K ends inside a long tile, for every length (the last tile is filled up with zeros on both operands)
+    (40, 1144, 72, "f16", dict(weight=True), "32x32x384_a0b0_w8"),
+    (40, 1000, 72, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),
+    (40, 520, 72, "f16", dict(weight=True), "32x32x128_a0b0_w8"),
+    (40, 252, 72, "f32", dict(weight=True), "32x32x128_a0b0_w8"),
+    (40, 132, 72, "f32", dict(weight=True), "32x32x64_a0b0_w8"),
+    # the lines between the forms, on either side
+    (64, 256, 80, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),
+    (64, 248, 80, "bf16", dict(weight=True), "64x64x64_a0b0"),
+    (64, 128, 80, "f32", dict(weight=True), "32x32x128_a0b0_w8"),
+    (64, 124, 80, "f32", dict(weight=True), "64x64x16_a0b0"),
+    (64, 256, 6144, "bf16", dict(weight=True), "32x32x64_a0b0"),             # 96 tiles of 64x64
+    (64, 256, 6208, "bf16", dict(weight=True), "64x64x64_a0b0_dma"),         # 97
+    (256, 768, 1024, "f16", dict(weight=True), "32x32x384_a0b0_w8"),         # one 32x32 tile per compute unit
+    (257, 768, 1024, "f16", dict(weight=True), "32x32x64_a0b0"),             # more: short tiles
+    (500, 1536, 768, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),        # more, and a long K
+    (1200, 768, 768, "f32", dict(weight=True), "32x32x128_a0b0_w8"),         # 228 tiles of 64x64
+    (64, 132, 16384, "f32", dict(weight=True), "64x64x16_a0b0"),             # 256, with too many zeros
+    (64, 128, 16384, "f32", dict(weight=True), "32x32x128_a0b0_w8"),         # 256
+    (64, 128, 16448, "f32", dict(weight=True), "64x128x16_a0b0"),             # 257
+    # operands read through the transposing loader, batched products
+    (96, 264, 64, "bf16", dict(batch=(4,)), "32x32x384_a0b1_w8"),
+    (100, 1000, 72, "f16", dict(batch=(2, 2)), "32x32x384_a0b1_w8"),
+    (70, 520, 64, "f16", dict(batch=(24,)), "32x32x384_a0b1_w8"),
+    (256, 512, 64, "bf16", dict(batch=(20,)), "32x32x256_a0b1_w8"),
+    (50, 132, 36, "f32", dict(batch=(3,)), "32x32x64_a0b1_w8"),
+    (200, 200, 64, "f32", dict(batch=(14,)), "32x32x128_a0b1_w8"),
+    (72, 256, 80, "f16", dict(a_transposed=True), "32x32x256_a1b1_w8"),
+    (72, 392, 80, "bf16", dict(a_transposed=True, weight=True), "32x32x256_a1b0_w8"),
+    (36, 140, 44, "f32", dict(a_transposed=True), "32x32x64_a1b1_w8"),
+    (36, 512, 44, "f32", dict(a_transposed=True, weight=True), "32x32x128_a1b0_w8"),
+    (704, 704, 768, "bf16", dict(a_transposed=True), "64x64x64_a1b1"),       # 132 tiles of 64x64
+    (1024, 300, 1024, "f32", dict(a_transposed=True, weight=True), "64x64x16_a1b0"),
+    # the product stored along its rows: the epilogue reads the eight partial tiles down their columns
+    (40, 768, 72, "bf16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8"),
+    (40, 384, 33, "f16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8"),
+    (72, 256, 64, "f16", dict(batch=(3,), out_transposed=True), "32x32x256_a0b1_w8"),
+    (44, 256, 36, "f32", dict(a_transposed=True, out_transposed=True), "32x32x128_a1b1_w8"),
+])
+def test_gemm_small_product_forms(M, K, N, dtype, kw, tile):
+    """The forms that products of few tiles take by default: tails of K, loaders, batches, both sides of every line."""
+    s, _ = check_against_oracle(U.product_block(M, K, N, dtype, **kw))
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
+    assert names == ["mfma_" + tile], names
 
 
 @pytest.mark.parametrize("tile", ["64,64,64,2,2,2,1,1", "128,64,64,2,2,2,1,1", "128,128,64,2,2,2,1,1", "256,128,64,4,2,2,1,1", "256,256,64,4,2,2,1,1",

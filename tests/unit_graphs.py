@@ -89,6 +89,25 @@ def gemm_block(M, K, N, dtype="f16", batch=(), bias=True, gelu=False, residual=F
     return b.finish()
 
 
+def product_block(M, K, N, dtype="f16", batch=(), a_transposed=False, weight=False, out_transposed=False, seed=42):
+    """a @ b: the left operand may be stored [K, M], the right one is stored [K, N] and may be an activation too (read
+    along N then), the product may be stored [N, M]."""
+    st = _st(seed)
+    b = GraphBuilder("product_block", dtype)
+    sa = batch + ((K, M) if a_transposed else (M, K))
+    lead = tuple(range(len(batch)))
+    swap = lead + (len(batch) + 1, len(batch))
+    x = b.input("x", sa, st.normal(sa, 0.0, 1.0, dtype))
+    if a_transposed:
+        x = configs._transpose(b, x, swap)
+    y = (b.weight if weight else b.input)("y", batch + (K, N), st.normal(batch + (K, N), 0.0, 1.0 / math.sqrt(K), dtype))
+    z = configs._un(b, "Relu", configs._matmul(b, x, y))
+    if out_transposed:
+        z = configs._transpose(b, z, swap)
+    b.mark_output(z)
+    return b.finish()
+
+
 def linear_layernorm_block(M, K, N, dtype="bf16", batch=(), residual=True, keep_sum=True, w_transposed=True, seed=37):
     """x @ w + bias (+ residual) -> LayerNorm over the last axis (decomposed) -> gamma, beta: a linear layer with the
     normalisation that follows it.  keep_sum: the sum in front of the normalisation is a graph output too (the

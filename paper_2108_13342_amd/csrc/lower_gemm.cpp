@@ -1263,9 +1263,9 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   // or two such workgroups per compute unit hide little from each other, so the kernel is the chain of its K tiles - a
   // memory round trip and two barriers each - and long tiles on eight wavefronts shorten it.  Product + bias, us, four
   // wavefronts on the short tile (K 64 in 16 bits, 16 in f32) against this form (M x K x N): bf16 33x3072x768
-  // 21.3 -> 14.3, 77x3072x768 18.4 -> 12.2, 33x768x3072 8.5 -> 7.5, 33x768x768 4.4 -> 4.3; f32 256x3072x768 62.0 ->
-  // 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Operands read element by element keep the short tile: a
-  // long one would not fit their registers.
+  // 21.3 -> 14.3, 77x3072x768 18.4 -> 12.2, 33x768x3072 8.5 -> 7.5 (7.1 on tiles of 256), 33x768x768 4.4 -> 4.3; f32
+  // 256x3072x768 62.0 -> 29.4, 256x768x2304 27.3 -> 21.2, 256x768x768 11.2 -> 7.5.  Operands read element by element keep
+  // the short tile: a long one would not fit their registers.
   // Where the line lies (64x64 tiles against this form): f32 up to one round of 64x64 tiles (256x768x3072, 192 tiles: 28.3,
   // 22.2; 1024x3072x1024, 256 tiles: 83.1, 72.6), 16-bit products of a K below 512 up to 96 tiles (200x384x1536: 4.6, 3.7;
   // 300x256x768: 3.8, 3.0).  A left operand that comes through the transposing loader is turned once for every column of

@@ -142,6 +142,7 @@ void decl_digits(std::ostringstream& os, const LowerCtx& c, const std::vector<in
 
 // shared by the MatMul and Conv templates
 std::string gemm_offset_fn(const LowerCtx& c, const std::string& name, const std::vector<int>& atoms, const Affine& a);
+std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads);
 const char* gemm_kernel_body();
 std::string gemm_epilogue_source(const LowerCtx& c, const std::vector<int>& batch, const std::vector<int>& rows,
                                  const std::vector<int>& cols, const std::map<int, int>& pslot, const std::string& kparams,

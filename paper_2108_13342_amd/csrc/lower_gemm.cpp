@@ -154,6 +154,22 @@ DEV cvec_t cvzero() { cvec_t v; for (int i = 0; i < B_CVEC; ++i) v[i] = 0; retur
 #if defined(CONV_DIRECT) && (BM != 32 || BN != 32 || WAVES_M != 1 || WAVES_N != 1 || ELEM_BYTES != 4)
 #error "direct convolution loop: one 32 x 32 fp32 tile per workgroup"
 #endif
+// 16 bytes a lane from global memory straight into LDS: lane l's go to byte lds + 16 l (lds: the same in every lane).
+// Written as assembly because of what the compiler does behind its own builtin: a fragment read that it cannot prove
+// to lie elsewhere in LDS waits for every load to LDS in flight (s_waitcnt vmcnt(0)), so each K tile's loads were
+// waited for as soon as they had been issued and no pipeline of tiles existed, whatever the number of buffers.  The
+// instruction has no register result that could be overwritten while it is in flight; the kernel waits for it by
+// count (VM_WAIT), and the counts the compiler places for loads of its own can only come out too strict.
+DEV void load_to_lds16(const void* g, const u32 lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"((unsigned long long)g), "s"(lds) : "m0");
+}
+DEV void load_to_lds4(const void* g, const u32 lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"((unsigned long long)g), "s"(lds) : "m0");
+}
+static __device__ __attribute__((aligned(16))) const u32 dn_zeros[4] = {0, 0, 0, 0};
+template <int N> struct int_c { static constexpr int v = N; };
+DEV u32 lds_address(void* p) { return __builtin_amdgcn_readfirstlane((u32)(unsigned long long)(__attribute__((address_space(3))) char*)p); }
+
 extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // one LDS allocation: the operand tiles during the main loop, an fp32 accumulator slab afterwards
 #ifdef W_PREFETCH_LINES
@@ -184,7 +200,7 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   idx_t t = bid % (tiles_m * tiles_n);
   // groups of 8 tile-rows walk the N direction together
   const idx_t grp = 8 * tiles_n, g0 = (t / grp) * 8;
-  const idx_t gsz = (tiles_m - g0) < 8 ? (tiles_m - g0) : 8;
+  const idx_t gsz = tiles_m < 8 ? tiles_m : (tiles_m % 8 == 0 || tiles_m - g0 >= 8) ? (idx_t)8 : tiles_m - g0;      // (a constant wherever it can be: it divides)
   const idx_t tile_m = g0 + (t % grp) % gsz, tile_n = (t % grp) / gsz;
   const idx_t row0 = tile_m * BM, col0 = tile_n * BN;
   const elem_t* __restrict__ Ab = PA + offA_batch(z);
@@ -192,22 +208,41 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #ifdef W_PREFETCH_LINES
   // The weight operand was last read an inference ago and comes from memory; fetched K tile by K tile, every step of
   // every workgroup's loop would wait for a memory round trip of its own.  Instead the workgroups of each XCD touch
-  // the whole matrix between them before anything else (one 4-byte load per 128-byte line, landing in a spare piece of
-  // LDS that nobody reads), so all of it is on its way into that XCD's L2 while the first tiles are being loaded.
-  {
-    typedef __attribute__((address_space(1))) const void* wpf_gptr_t;
-    typedef __attribute__((address_space(3))) void* wpf_lptr_t;
-    const idx_t nx = (gridDim.x + 7) / 8, j = blockIdx.x / 8;
-    const idx_t per = (W_PREFETCH_LINES + nx - 1) / nx;
-    for (idx_t i = tid; i < per; i += NT) {
-      const idx_t line = j * per + i;
-      if (line < W_PREFETCH_LINES)
-        __builtin_amdgcn_global_load_lds((wpf_gptr_t)((const char*)W_PREFETCH_PTR + line * 128),
-                                         (wpf_lptr_t)(smem + SMEM_MAIN + (RA ? 4 * BM : 0)), 4, 0, 0);
-    }
-  }
+  // what their tiles will read of the matrix between them (one 4-byte load per 128-byte line, landing in a spare piece
+  // of LDS that nobody reads), so all of it is on its way into that XCD's L2 while the first tiles are being loaded.
+  // The tiles of an XCD are consecutive: inside one group of tile-rows they cover a run of columns, otherwise all.
+  // In the direct-to-LDS loop every wavefront issues W_PF_N loads (lanes past its share touch the last line again): they are
+  // counted there.
+  auto touch_weights = [&]() {
+    const idx_t nb = tiles_m * tiles_n, x = blockIdx.x % 8, nx = nb / 8 + (x < nb % 8 ? 1 : 0);
+    const idx_t t0 = bid - blockIdx.x / 8, t1 = t0 + nx - 1;
+    const bool one = t0 / grp == t1 / grp;
+#ifdef W_PF_ROWS
+    // (a filter matrix is the left operand: the tile-rows of the group, or, inside one column, those from tile to tile)
+    const bool column = one && (t0 % grp) / gsz == (t1 % grp) / gsz;
+    const idx_t lo = one ? (g0 + (column ? (t0 % grp) % gsz : 0)) * BM : 0, hi = one ? (g0 + (column ? (t1 % grp) % gsz + 1 : gsz)) * BM : GM;
+    const bool to_end = hi >= GM;
+#else
+    const idx_t lo = one ? (t0 % grp) / gsz * BN : 0, hi = one ? ((t1 % grp) / gsz + 1) * BN : GN;
+    const bool to_end = hi >= GN;
 #endif
-
+    const idx_t l0 = (idx_t)((long long)lo * GK * ELEM_BYTES / 128), l1 = to_end ? (idx_t)W_PREFETCH_LINES : (idx_t)((long long)hi * GK * ELEM_BYTES / 128);
+    const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
+    const idx_t per = (l1 - l0 + nx - 1) / nx, first = l0 + (blockIdx.x / 8) * per, end = first + per < l1 ? first + per : l1;
+#pragma unroll
+    for (int i = 0; i < W_PF_N; ++i) {
+      const idx_t line = first + tid + i * NT;
+#ifdef DMA
+      load_to_lds4((const char*)W_PREFETCH_PTR + (long long)(line < end ? line : l1 - 1) * 128, spare);
+#else
+      if (line < end) load_to_lds4((const char*)W_PREFETCH_PTR + (long long)line * 128, spare);
+#endif
+    }
+  };
+#else
+#define W_PF_N 0
+  auto touch_weights = [&]() {};
+#endif
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -226,15 +261,16 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #define WHOLE(n) ((n) % NT == 0)                         // every thread has work in each pass over n items
   const int nk = (GK + BK - 1) / BK;
 #ifdef DMA
-  // Both operands contiguous along K, 16-bit, K a multiple of BK: the tiles go from global memory straight
-  // into LDS (global_load_lds, 16 bytes per lane), past the registers and without LDS store instructions.
-  // One such instruction of a wavefront fills 1 KB of consecutive LDS: 64 / (BK / 8) rows of BK elements,
-  // unpadded.  Fragment reads stay conflict-free because the 16-byte chunks of a row are stored permuted:
-  // chunk c of row r sits in slot c ^ f(r), f(r) = (r ^ (r >> 3)) & (BK / 8 - 1) -- any 8 or 16
-  // consecutive rows then meet different banks at the same c.  The permutation costs nothing: each lane
-  // simply fetches the global chunk that belongs in its slot.
+  // Both operands contiguous along K: the tiles go from global memory straight into LDS (global_load_lds, 16 bytes
+  // per lane), past the registers and without LDS store instructions.  One such instruction of a wavefront fills 1 KB
+  // of consecutive LDS, rows of BK elements, unpadded.  Fragment reads stay conflict-free because the 16-byte chunks of
+  // a row are stored permuted: chunk c of row r sits in slot c ^ f(r).  Rows of 128 bytes: f(r) = (r ^ (r >> 3)) & 7,
+  // and the halves of a 256-byte line of banks are told apart by the row's parity; rows of whole 256-byte lines:
+  // f(r) = r & 15.  Any 16 consecutive rows then meet different banks at the same c.  The permutation costs nothing:
+  // each lane simply fetches the global chunk that belongs in its slot.  Where K ends inside a tile, the chunks behind
+  // its end come from 16 bytes of zeros.
 #define CPR (BK / VEC)                                   // 16-byte chunks per tile row
-#define SWZ(r) ((((r) ^ ((r) >> 3))) & (CPR - 1))
+#define SWZ(r) (CPR % 16 == 0 ? (r) & 15 : (((r) ^ ((r) >> 3))) & (CPR - 1))
   idx_t ra_off[A_DIRECT_N], rb_off[B_DIRECT_N];
   int ra_k[A_DIRECT_N], rb_k[B_DIRECT_N];
 #pragma unroll
@@ -249,24 +285,95 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
     rb_off[i] = offB_col(COL_B(r));
     rb_k[i] = ((v % CPR) ^ SWZ(r)) * VEC;
   }
-  typedef __attribute__((address_space(1))) const void* gptr_t;
-  typedef __attribute__((address_space(3))) void* lptr_t;
   auto dma_load = [&](const int buf, const idx_t k0) {
+    const u32 la = lds_address((char*)&As[buf][0][0] + wave * 1024), lb = lds_address((char*)&Bs[buf][0][0] + wave * 1024);
 #pragma unroll
-    for (int i = 0; i < A_DIRECT_N; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(Ab + ra_off[i] + offA_k(k0 + ra_k[i])),
-                                       (lptr_t)((char*)&As[buf][0][0] + (i * NT + wave * 64) * 16), 16, 0, 0);
+    for (int i = 0; i < A_DIRECT_N; ++i) {
+      const idx_t k = k0 + ra_k[i];
+      load_to_lds16(FULL_K || k < GK ? (const void*)(Ab + ra_off[i] + offA_k(k)) : (const void*)dn_zeros, la + i * NT * 16);
+    }
 #pragma unroll
-    for (int i = 0; i < B_DIRECT_N; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(Bb + rb_off[i] + offB_k(k0 + rb_k[i])),
-                                       (lptr_t)((char*)&Bs[buf][0][0] + (i * NT + wave * 64) * 16), 16, 0, 0);
+    for (int i = 0; i < B_DIRECT_N; ++i) {
+      const idx_t k = k0 + rb_k[i];
+      load_to_lds16(FULL_K || k < GK ? (const void*)(Bb + rb_off[i] + offB_k(k)) : (const void*)dn_zeros, lb + i * NT * 16);
+    }
   };
-  // Tile kt is multiplied from buffer kt & 1, one 16-deep K step at a time, with two sets of fragment registers:
+#define LDS_WAIT() { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(0xC07F); __builtin_amdgcn_sched_barrier(0); }   /* lgkmcnt(0) */
+#define VM_WAIT(n) { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14)); __builtin_amdgcn_sched_barrier(0); }
+  // The barrier alone: __syncthreads() is a release too, for which the compiler waits until no load is outstanding
+  // (s_waitcnt vmcnt(0) in front of s_barrier), and the tiles behind the next one would never be in flight across it.
+  // Everything this barrier orders has been waited for in front of it: the loads of the tile that it opens by VM_WAIT,
+  // this wavefront's fragment reads by LDS_WAIT.
+#define TILE_BARRIER() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); asm volatile("" ::: "memory"); }
+  // NBUF buffers: tile kt lives in buffer kt % NBUF and the loads run DMA_D = NBUF - 1 tiles ahead of the multiplications
+  // (one where K does not hold the 2 DMA_D - 1 tiles that the schedule is written for).  A wavefront's loads complete in
+  // order, so "tile kt has landed" is a wait until at most the loads issued behind it are outstanding.
+  // What the pipeline is worth, 64x64 tiles with two buffers whose loads were waited for at once, with two and with three
+  // buffers, us with bias: bf16 1024x3072x768 36.9, 26.6, 15.9; 4096x3072x768 39.6, 34.3, 35.6 (128x128 on three buffers
+  // 49.0, 28.4); 1024x768x768 8.9, 6.4, 5.9; 256x768x2304 7.2, 6.4, 5.8.
+#define DMA_NK ((GK + BK - 1) / BK)
+#define DMA_D (DMA_NK >= 2 * NBUF - 3 ? NBUF - 1 : 1)
+#define DMA_LPT (A_DIRECT_N + B_DIRECT_N)                 // load instructions per wavefront and tile
+  // Tiles 0 .. DMA_D - 1 are issued first, the touches of the weight operand behind them, the other tiles one by one in
+  // the loop; a tile of the first group has landed when what was issued behind it may still be outstanding.
+#pragma unroll
+  for (int d = 0; d < DMA_D; ++d) dma_load(d, (idx_t)d * BK);
+  touch_weights();
+  constexpr int_c<0> no{};
+  constexpr int_c<1> yes{};
+  constexpr int_c<(DMA_D - 1) * DMA_LPT + W_PF_N> behind_touches{};
+  constexpr int_c<(DMA_D - 1) * DMA_LPT> steady{};
+  int buf = 0;
+#if WAVES_K > 1
+  // Wavefronts that split K: step s of a tile belongs to wavefront s % WAVES_K.  A tile is opened by the wait for this
+  // wavefront's share of its loads and a barrier, behind which everybody has left the tile in front of it, too: that
+  // one's buffer takes the loads of tile kt + DMA_D.  One barrier a tile, DMA_D tiles of loads in flight.
+#define KQ (BK / (ELEM_BYTES == 2 ? 16 : 8) / WAVES_K)
+  auto k_tile = [&](const int kt, auto load_, auto wait_) {
+    constexpr int LOAD = decltype(load_)::v, WAIT = decltype(wait_)::v;
+    VM_WAIT(WAIT)
+    TILE_BARRIER();
+    if constexpr (LOAD) { int nb = buf + DMA_D; if (nb >= NBUF) nb -= NBUF; dma_load(nb, (idx_t)(kt + DMA_D) * BK); }
+    vec_t fa[KQ], fb[KQ];
+    const int fr = lane & 31;
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+      const int c = (q * WAVES_K + wk) * 2 + (lane >> 5);
+      fa[q] = *(const vec_t*)&As[buf][fr][(c ^ SWZ(fr)) * VEC];
+      fb[q] = *(const vec_t*)&Bs[buf][fr][(c ^ SWZ(fr)) * VEC];
+    }
+    LDS_WAIT();
+    asm volatile("" ::: "memory");                        // (the reads stay in front of the next tile's barrier)
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) {
+#if ELEM_BYTES == 2
+      acc[0][0] = MFMA(__builtin_bit_cast(frag_t, fa[q]), __builtin_bit_cast(frag_t, fb[q]), acc[0][0], 0, 0, 0);
+#else
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q][e], fb[q][e], acc[0][0], 0, 0, 0);
+#endif
+    }
+    buf = buf + 1 < NBUF ? buf + 1 : 0;
+  };
+  constexpr int n_head = DMA_D < DMA_NK - DMA_D ? DMA_D : DMA_NK - DMA_D;
+#pragma unroll
+  for (int kt = 0; kt < n_head; ++kt) k_tile(kt, yes, behind_touches);
+#pragma unroll 1
+  for (int kt = DMA_D; kt < nk - DMA_D; ++kt) k_tile(kt, yes, steady);
+#if DMA_D >= 3
+  k_tile(nk - 3, no, int_c<2 * DMA_LPT>{});
+#endif
+#if DMA_D >= 2
+  k_tile(nk - 2, no, int_c<DMA_LPT>{});
+#endif
+  k_tile(nk - 1, no, no);
+#else
+  // Tile kt is multiplied one 16-deep K step at a time, with two sets of fragment registers:
   // while the MFMAs of step s run, the fragment reads of step s + 1 are already in flight (one wait per step,
   // after the MFMAs have been issued).  The reads that follow a tile's last step belong to the next tile: before
   // them the wavefront waits for its share of that tile's loads and meets the others (one barrier per tile), and
-  // since every wavefront has then finished reading the current buffer, the loads of the tile after next start
-  // into it right away - a whole tile of MFMA work ahead of their use.
+  // since every wavefront has then finished reading the current buffer, the loads of the tile NBUF further on start
+  // into it right away.
 #define KSTEPS (BK / 16)
   frag_t fa[2][TM], fb[2][TN];
   int fra[TM], frb[TN];                                    // row offsets of this lane's fragments, and the rows' swizzles
@@ -284,55 +391,28 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) fb[set][j] = __builtin_bit_cast(frag_t, *(const u16x8*)(bb + frb[j] + (kc ^ fsb[j]) * VEC));
   };
-#define LDS_WAIT() { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(0xC07F); __builtin_amdgcn_sched_barrier(0); }   /* lgkmcnt(0) */
-  // NBUF buffers: tile kt lives in buffer kt % NBUF and the loads run NBUF - 1 tiles ahead of the multiplications (two
-  // buffers: one tile ahead - enough for operands that sit in the caches; three or four: for operands that another
-  // kernel has just written, whose loads take several tile times to arrive).  A wavefront's loads complete in order, so
-  // "tile kt + 1 has landed" is a wait until at most the loads of the tiles behind it are outstanding.
-#define DMA_LPT (A_DIRECT_N + B_DIRECT_N)                 // load instructions per wavefront and tile
-#define DMA_D (NBUF - 1)
-#define VM_WAIT(n) { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14)); __builtin_amdgcn_sched_barrier(0); }
-  auto wait_tiles = [&](const int behind) {               // at most `behind` later tiles may still be in flight
-    if (DMA_D >= 3 && behind >= 2) VM_WAIT(2 * DMA_LPT)
-    else if (DMA_D >= 2 && behind == 1) VM_WAIT(DMA_LPT)
-    else VM_WAIT(0)
-  };
-#pragma unroll
-  for (int d = 0; d < DMA_D; ++d) if (d < nk) dma_load(d, (idx_t)d * BK);
-  wait_tiles((nk < DMA_D ? nk : DMA_D) - 1);
-  __syncthreads();
-  frag_load(0, 0, 0);
-  LDS_WAIT();
   // Wavefronts with at least as many matrix instructions as fragment reads per step (64x64 results and more): inside a
   // tile the reads of the next step are issued between the matrix instructions of the current one (one read after each
-  // matrix instruction, in program order), and the K loop stays rolled - unrolled over a short constant K the address
-  // arithmetic of every tile is hoisted and the registers spill.  Smaller wavefront tiles keep the block order (reads,
-  // then matrix instructions), which measured faster for them.
+  // matrix instruction, in program order).  Smaller wavefront tiles keep the block order (reads, then matrix
+  // instructions), which measured faster for them.
 #define N_MF (TM * TN)
 #define N_RD (TM + TN)
-#if N_MF >= N_RD || NBUF > 2
-#define DMA_ROLLED 1
-#endif
 #if N_MF >= N_RD
 #define DMA_INTERLEAVE 1
 #endif
-  int buf = 0;
-#ifdef DMA_ROLLED
-#pragma unroll 1
-#endif
-  for (int kt = 0; kt < nk; ++kt) {
-    // everybody has left tile kt - 1 (the barrier that opened this tile): its buffer takes tile kt + NBUF - 1
-    if (kt + DMA_D < nk) { int nb = buf + DMA_D; if (nb >= NBUF) nb -= NBUF; dma_load(nb, (idx_t)(kt + DMA_D) * BK); }
+  // One K tile.  LOAD: the loads of tile kt + DMA_D start here.  WAIT: how many loads may still be outstanding when the
+  // next tile is opened, -1: no tile follows.
+  auto k_tile = [&](const int kt, auto load_, auto wait_) {
+    constexpr int LOAD = decltype(load_)::v, WAIT = decltype(wait_)::v;
+    // everybody has left tile kt - 1 (the barrier that opened this tile): its buffer is free
+    if constexpr (LOAD) { int nb = buf + DMA_D; if (nb >= NBUF) nb -= NBUF; dma_load(nb, (idx_t)(kt + DMA_D) * BK); }
     int nxt = buf + 1; if (nxt >= NBUF) nxt = 0;
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) {
       if (kk + 1 < KSTEPS) frag_load(buf, kk + 1, (kk + 1) & 1);
-      else if (kt + 1 < nk) {
-        // this wavefront's share of tile kt + 1 is in LDS (the tiles up to min(kt + NBUF - 1, nk - 1) may stay in flight),
-        const int last = kt + DMA_D < nk ? kt + DMA_D : nk - 1;
-        wait_tiles(last - (kt + 1));
-        __syncthreads();                                 // so is everybody's, and nobody reads `buf` any more
-        __builtin_amdgcn_sched_barrier(0);
+      else if constexpr (WAIT >= 0) {
+        VM_WAIT(WAIT)                                    // this wavefront's share of tile kt + 1 is in LDS,
+        TILE_BARRIER();                                  // so is everybody's, and nobody reads `buf` any more
         frag_load(nxt, 0, 0);                            // KSTEPS is even: step 0 of the next tile uses set 0
       }
 #ifndef DMA_INTERLEAVE
@@ -357,7 +437,27 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
       LDS_WAIT();
     }
     buf = nxt;
-  }
+  };
+  VM_WAIT((DMA_D - 1) * DMA_LPT + W_PF_N)
+  TILE_BARRIER();
+  frag_load(0, 0, 0);
+  LDS_WAIT();
+#if DMA_D >= 2
+  k_tile(0, yes, behind_touches);
+#endif
+#if DMA_D >= 3
+  k_tile(1, yes, behind_touches);
+#endif
+#pragma unroll 1
+  for (int kt = DMA_D - 1; kt < nk - DMA_D; ++kt) k_tile(kt, yes, steady);
+#if DMA_D >= 3
+  k_tile(nk - 3, no, int_c<DMA_LPT>{});
+#endif
+#if DMA_D >= 2
+  k_tile(nk - 2, no, no);
+#endif
+  k_tile(nk - 1, no, int_c<-1>{});
+#endif   // WAVES_K
 #elif defined(CONV_DIRECT)
   // A convolution with too few 32 x 32 tiles to fill the chip is one memory round trip plus a chain of matrix
   // instructions, and staging K tile by K tile through LDS turns that into a chain of round trips.  Here K
@@ -664,6 +764,7 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // tiles are loaded ahead, so the latency of a tile's global loads overlaps PF - 1 tiles of MFMA work.
 #pragma unroll
   for (int s = 0; s < PF; ++s) gload(s, (idx_t)s * BK);
+  touch_weights();
   lstore(0, 0, 0);
   __syncthreads();
   for (int kt0 = 0; kt0 < nk; kt0 += PF) {
@@ -698,6 +799,10 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // consecutive lanes: its loads and stores coalesce into full lines, whatever index map the
   // block's Reorganize/Shuffle operators imposed on the destination.
   float* Cs = (float*)smem;
+#if defined(W_PREFETCH_LINES) && (defined(DMA) || (GK + BK - 1) / BK <= PF)
+  // no touch is in flight to this workgroup's LDS when it ends (a longer register-staged loop has waited for loads behind them)
+  __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
+#endif
 #if RA
   // per row of the tile: position of its first column inside a 16-byte group of the destination.  The table lies behind
   // the operand tiles, so it can be filled while other wavefronts still multiply; the slab loop's first barrier publishes it.
@@ -860,6 +965,31 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 }  // namespace
 
 const char* gemm_kernel_body() { return kGemmBody; }
+
+// The macros that make a kernel touch its weight operand up front (see touch_weights in the kernel): `lines` 128-byte lines
+// of parameter `slot`, `rows`: the left operand.  W_PF_N covers the largest share of any XCD, up to what the wait counts hold.
+std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads) {
+  const int64_t nb = tiles_m * tiles_n, grp = 8 * tiles_n;
+  int64_t most = 1;
+  for (int64_t x = 0, t0 = 0; x < 8; x++) {
+    const int64_t nx = nb / 8 + (x < nb % 8 ? 1 : 0);
+    if (!nx) continue;
+    const int64_t t1 = t0 + nx - 1, g0 = t0 / grp * 8, gsz = std::min<int64_t>(8, tiles_m - g0);
+    int64_t lo = 0, hi = rows ? GM : GN;
+    if (t0 / grp == t1 / grp) {
+      const int64_t c0 = (t0 % grp) / gsz, c1 = (t1 % grp) / gsz;
+      if (!rows) { lo = c0 * BN; hi = (c1 + 1) * BN; }
+      else { lo = (g0 + (c0 == c1 ? (t0 % grp) % gsz : 0)) * BM; hi = (g0 + (c0 == c1 ? (t1 % grp) % gsz + 1 : gsz)) * BM; }
+    }
+    const int64_t n = (hi >= (rows ? GM : GN) ? lines : hi * row_bytes / 128) - lo * row_bytes / 128;
+    most = std::max(most, (n + nx * threads - 1) / (nx * threads));
+    t0 += nx;
+  }
+  std::ostringstream k;
+  k << "#define W_PREFETCH_LINES " << lines << "\n#define W_PREFETCH_PTR p" << slot << "\n#define W_PF_N " << std::min<int64_t>(most, 24) << "\n";
+  if (rows) k << "#define W_PF_ROWS 1\n";
+  return k.str();
+}
 
 // Source of the generated epilogue functions shared by the MatMul and Conv kernels:
 //   col_loads()    operands addressed by the column alone (bias vectors, ...), loaded once per thread
@@ -1225,22 +1355,41 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   }
   // both operands contiguous along K and K a whole number of tiles: tiles loaded straight into LDS
   const bool dma_ok = eb == 2 && amode == 0 && bmode == 0 && K % 64 == 0 && !getenv("DNNF_GEMM_NO_DMA");   // (developer switch for A/B runs)
+  // Time model of the direct-to-LDS forms, us: t0 + the rounds of workgroups that the chip's compute units hold at once,
+  // each nk * max(a0, r * a1) + b with r workgroups on a unit (a0: one alone, bound by its own chain of waits; a1: the unit's
+  // share when it is full; b: first loads and epilogue).  Fitted to 35 products (M 256 .. 8192, K 128 .. 3072, N 128 .. 3072,
+  // weights from beyond the L2 caches) on every form, 5 to 12 % rms each; the form it names is 3 % slower than the best of
+  // the nine on average, where the cycle model below was 16 %, and 67 % at worst (512x128x128 and larger tiles for few tiles
+  // of a long K: 2048x1536x384 15.1 against 8.9).
+  struct Fit { double t0, a0, a1, b; };
+  std::vector<Fit> fits(cands.size());
   if (dma_ok) {
-    cands.push_back({64, 64, 64, 2, 2, 1, 2, 1, 1});
-    // larger tiles on the same loop: 128 KB / 64 KB of LDS for the two buffers, eight wavefronts on the 256x256
-    // tile (two per SIMD, 64x128 results each), four on 128x128
-    cands.push_back({256, 256, 64, 4, 2, 1, 2, 1, 1});
-    cands.push_back({128, 128, 64, 2, 2, 1, 2, 1, 1});
-    // the same loop with eight wavefronts per workgroup
-    cands.push_back({128, 128, 64, 2, 4, 1, 2, 1, 1});
-    cands.push_back({64, 128, 64, 2, 4, 1, 2, 1, 1});
-    cands.push_back({128, 64, 64, 4, 2, 1, 2, 1, 1});
-    cands.push_back({256, 256, 64, 4, 4, 1, 2, 1, 1});
+    // tile, wavefronts, buffers: 128 bytes of K a row, so a 64x64 tile on three buffers takes 48 KB of LDS (three workgroups on
+    // a compute unit), 128x128 on two 64 KB (two) and on three 96 KB (one)
+    auto add = [&](int bm, int bn, int wm, int wn, int nbuf, Fit fit) { cands.push_back({bm, bn, 64, wm, wn, 1, nbuf, 1, 1}); fits.push_back(fit); };
+    add(64, 64, 2, 2, 2, {1.81, 0.352, 0.225, 0.81});
+    add(64, 64, 2, 2, 3, {1.53, 0.260, 0.214, 1.13});
+    add(64, 64, 2, 2, 4, {1.69, 0.255, 0.210, 0.98});
+    add(64, 128, 2, 4, 3, {1.00, 0.324, 0.326, 1.90});
+    add(128, 64, 4, 2, 3, {1.14, 0.301, 0.319, 1.78});
+    add(128, 128, 2, 4, 2, {1.00, 0.541, 0.612, 1.98});
+    add(128, 128, 2, 4, 3, {1.00, 0.499, 0.300, 2.39});
+    add(256, 128, 4, 2, 3, {1.00, 0.667, 0.891, 3.33});
+    add(256, 256, 4, 2, 2, {1.00, 1.290, 1.398, 4.54});
   }
   // Default choice: a cost model in cycles per CU.  A K tile costs the larger of its MFMA time and its
   // LDS time (16-byte fragment reads at 128 B/clk, stores at 64 B/clk) plus a fixed barrier/latency
   // share; tiles are dealt to 256 CUs, and partly filled rounds count in full.
-  auto cost = [&](const Cfg& f) {
+  auto cost = [&](size_t ci) {
+    const Cfg& f = cands[ci];
+    if (dma_ok) {
+      if (!f.DMA) return 1e30;
+      const Fit& m = fits[ci];
+      const int lds = f.NBUF * (f.BM + f.BN) * 128 + 512, occ = std::min((160 << 10) / lds, 32 / (f.WM * f.WN));
+      const double nkt = (double)(K / 64), n = (double)nblocks(f.BM, f.BN) / 256.0;
+      const double full = std::floor(n / occ), rest = std::ceil(n - full * occ);
+      return m.t0 + full * (nkt * std::max(m.a0, occ * m.a1) + m.b) + (rest > 0 ? nkt * std::max(m.a0, rest * m.a1) + m.b : 0.0);
+    }
     const double tm = f.BM / f.WM / 32.0, tn = f.BN / f.WN / 32.0, steps = f.BK / 16.0;
     const double mfma = tm * tn * steps * (eb == 2 ? 32.0 : 512.0) * (f.WM * f.WN / 4.0);   // wavefronts share 4 SIMDs
     const double lds_rd = f.WM * f.WN * (tm + tn) * steps * 8.0;
@@ -1248,7 +1397,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     const double nkt = (double)((K + f.BK - 1) / f.BK);
     const double per_tile = nkt * (std::max(mfma, lds_rd + lds_wr) + 120.0) + f.BM * f.BN / 16.0 + 1500.0;
     const double rounds = std::ceil((double)nblocks(f.BM, f.BN) / 256.0);
-    return rounds * per_tile * (f.DMA ? 0.9 : 1.0);
+    return rounds * per_tile;
   };
   int pick = 0;
   if (c.opts.force_variant >= 100) {
@@ -1256,7 +1405,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     pick = c.opts.force_variant - 100;
   } else {
     for (size_t i = 1; i < cands.size(); i++)
-      if (cost(cands[i]) < cost(cands[pick])) pick = (int)i;
+      if (cost(i) < cost((size_t)pick)) pick = (int)i;
   }
   Cfg f = cands[pick];
   // A problem too small to occupy the chip with 64x64 tiles: 32x32 tiles whose wavefronts split K between them.  One
@@ -1296,7 +1445,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // 18.2 (19.9), 17.6 (19.1)) or the right operand larger than an L2 cache of 4 MB (128x768x3072: 8.5 (9.9), 8.1 (9.6);
     // 96x1024x4096: 14.1 (15.2), 13.2 (14.2)); between 2 and 4 MB it is one way in a loop and the other in a row
     // (300x768x2304: 6.3 (9.1), 6.7 (8.8)).
-    const bool long_16 = !direct || n32 <= 256 || K >= 1536 || (K >= 512 && GZ * GN * K * eb > (4 << 20));
+    const bool long_16 = !direct || n32 <= 256 || K >= 1536 || (K >= 512 && n32 > 320 && GZ * GN * K * eb > (4 << 20));
     // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
     // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile
     // costs what `share` values of K would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5,
@@ -1306,7 +1455,17 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // does not hold K in one or two tiles loses as soon as there are so many (eight products 896x896x64, 448 workgroups:
     // 10.2, 8.8, 11.4; 15 of 768x768x64, 720: 14.6, 10.0, 10.8).  Tiles of 512 in 16 bits and of 192 or 256 in f32 were no
     // faster in any product.
-    if (vec_loads && eb == 4 && !zeros) f = {32, 32, bk_f32, 1, 1, 8, 1, 2};
+    if (vec_loads && eb == 4 && !zeros) {
+      f = {32, 32, bk_f32, 1, 1, 8, 1, 2};
+      // Both operands along K and no more workgroups than compute units: straight into LDS, tiles of 64 on four buffers where K
+      // is long and whole, else what the padding asks for on three.  Register-staged and this, us: 256x3072x768 19.9, 17.4;
+      // 256x768x768 7.1, 6.3; 33x768x768 7.0, 6.2; 64x384x1536 5.2, 4.8; 256x132x768 3.8, 3.3.  With more workgroups the matrix
+      // cores are the bound and registers hold what LDS would: 256x768x3072 15.0, 16.7; 1024x768x768 15.0, 16.9.
+      if (direct && n32 <= 256 && !getenv("DNNF_GEMM_NO_DMA")) {
+        if (K % 64 == 0 && K >= 512) f = {32, 32, 64, 1, 1, 8, 4, 2, 1};
+        else f = {32, 32, bk_f32, 1, 1, 8, 3, 2, 1};
+      }
+    }
     else if (vec_loads && eb == 2 && long_16) {
       const int share = direct ? 18 : 150;
       const int64_t n384 = (K + 383) / 384;
@@ -1316,6 +1475,13 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
         const int64_t work = (K + bk - 1) / bk * (bk + share);
         if (!least || work < least) { least = work; f = {32, 32, bk, 1, 1, 8, 1, 2}; }
       }
+    }
+    // 16 bits, both operands along K: the same tiles straight into LDS, as many tiles of loads in flight as leave a compute unit
+    // the workgroups that it gets.  Register-staged and this, us: 33x3072x768 7.7, 6.9; 33x768x2304 4.2, 3.9; 77x768x768 4.0, 3.6;
+    // 200x1536x384 5.2, 4.5; 500x768x768 4.8, 4.3; 257x768x1024 5.5, 4.7; 900x768x768 6.8, 6.4; 300x768x2304 8.2, 7.5.
+    if (vec_loads && eb == 2 && direct && !getenv("DNNF_GEMM_NO_DMA")) {
+      f.DMA = 1;
+      f.NBUF = f.WK == 4 ? 4 : f.BK == 384 ? 3 : f.BK == 256 ? (n32 <= 256 ? 3 : 2) : (n32 <= 256 ? 4 : 3);
     }
   }
   int BM = f.BM, BN = f.BN, BK = f.BK, WAVES_M = f.WM, WAVES_N = f.WN, WAVES_K = f.WK, NBUF = f.NBUF, PF = f.PF, DMA = f.DMA;
@@ -1328,9 +1494,13 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
         v[0] % (32 * v[3]) == 0 && v[1] % (32 * v[4]) == 0 && v[2] % (eb == 2 ? 16 : 4) == 0 && (v[5] == 1 || v[5] == 2 || (v[7] == 1 && v[5] <= 4 && v[5] >= 1))) {
       BM = v[0]; BN = v[1]; BK = v[2]; WAVES_M = v[3]; WAVES_N = v[4]; NBUF = v[5]; WAVES_K = std::max(1, 4 / (v[3] * v[4]));
       if (v[6] >= 1 && v[6] <= 4) PF = v[6];
-      DMA = v[7] == 1 && dma_ok && BK == 64 && NBUF >= 2 && WAVES_K == 1;
+      if (v[7] == 1 && v[3] * v[4] == 1 && amode == 0 && bmode == 0 && NBUF >= 2) { WAVES_K = 4 * std::max(1, v[6]); DMA = 1; }      // K split: four or eight wavefronts
+      else DMA = v[7] == 1 && dma_ok && BK == 64 && NBUF >= 2 && WAVES_K == 1;
     }
   }
+  // (a tile's name says the number of buffers where it was asked for - by a tuning build or the override - and not where it is
+  // the choice made here; the tiles whose wavefronts split K are named by tile and wavefronts alone)
+  const bool named_buffers = c.opts.force_variant >= 100 || getenv("DNNF_GEMM_TILE");
   int norm_value = -1;        // expression node of the value the normalisation reads
   if (norm) {
     // eight wavefronts side by side on 32 whole rows of the product
@@ -1357,7 +1527,11 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     DNNF_CHECK(norm_value >= 0, DNNF_UNSUPPORTED_OP, "the normalised tensor is not produced by the product's part of the block");
   }
   // a wavefront's load instruction fills 64 whole 16-byte slots of the tile: no partly used pass
-  if (DMA) DNNF_CHECK((BM * BK / 8) % (64 * WAVES_M * WAVES_N) == 0 && (BN * BK / 8) % (64 * WAVES_M * WAVES_N) == 0, DNNF_UNSUPPORTED_OP, "tile does not divide into whole load passes");
+  if (DMA) {
+    const int vec = 16 / eb, nt = 64 * WAVES_M * WAVES_N * WAVES_K;
+    DNNF_CHECK((BM * BK / vec) % nt == 0 && (BN * BK / vec) % nt == 0, DNNF_UNSUPPORTED_OP, "tile does not divide into whole load passes");
+    DNNF_CHECK(amode == 0 && bmode == 0 && (WAVES_K > 1 || (eb == 2 && K % BK == 0)) && NBUF >= 2 && NBUF <= 4, DNNF_UNSUPPORTED_OP, "operands cannot be loaded straight into LDS");
+  }
 
   // parameters: A, B, epilogue loads, outputs
   std::vector<int> params = {ta, tb};
@@ -1422,7 +1596,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     const int64_t wbytes = TBt.n() * dtype_bytes(TBt.dtype);
     if (!norm && GZ == 1 && (TBt.kind == DNNF_WEIGHT || TBt.weight_only) && wbytes >= (256 << 10) && wbytes <= ((int64_t)16 << 20) &&
         wbytes == GN * K * eb && !getenv("DNNF_NO_WEIGHT_PREFETCH"))      // (developer switch for A/B runs)
-      k << "#define W_PREFETCH_LINES " << wbytes / 128 << "\n#define W_PREFETCH_PTR p1\n";
+      k << weight_touch_macros(wbytes / 128, 1, false, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K * eb, 64 * WAVES_M * WAVES_N * WAVES_K);
   }
   if (TA.dtype == DNNF_F16) k << "typedef f16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_f16\n";
   else if (TA.dtype == DNNF_BF16) k << "typedef bf16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_bf16\n";
@@ -1493,7 +1667,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   Kn.source = src;
   Lw.launches.push_back(Kn);
   Lw.variant = "mfma_" + std::to_string(BM) + "x" + std::to_string(BN) + "x" + std::to_string(BK) + "_a" + std::to_string(amode) + "b" + std::to_string(bmode) +
-               (WAVES_M * WAVES_N * WAVES_K > 4 ? "_w" + std::to_string(WAVES_M * WAVES_N * WAVES_K) : std::string()) + (DMA ? (NBUF > 2 ? "_dma" + std::to_string(NBUF) : std::string("_dma")) : std::string()) + (norm ? "_rownorm" : "");
+               (WAVES_M * WAVES_N * WAVES_K > 4 ? "_w" + std::to_string(WAVES_M * WAVES_N * WAVES_K) : std::string()) + (DMA && WAVES_K == 1 ? (NBUF > 2 && named_buffers ? "_dma" + std::to_string(NBUF) : std::string("_dma")) : std::string()) + (norm ? "_rownorm" : "");
   return Lw;
 }
 

@@ -835,17 +835,34 @@ Lowered lower_conv(LowerCtx& c) {
       k << "  const int kw_ = (int)(kk % " << KW << "), kh_ = (int)((kk / " << KW << ") % " << KH << ");\n";
       k << "  const idx_t a" << xc << " = kk / " << KH * KW << ", a" << xn << " = g.n;\n";
       }
-      // (a branch-free form - clamped address, value zeroed afterwards - was measured and is a few percent slower
-      // here: the compiler already keeps a tile's gathers in flight together, and the clamps are extra work)
-      k << "  const idx_t a" << xh << " = g.h0 + kh_;\n";
-      k << "  const idx_t a" << xw << " = g.w0 + kw_;\n";
-      k << "  if (a" << xh << " < 0 || a" << xh << " >= " << H << " || a" << xw << " < 0 || a" << xw << " >= " << Wd << ") return (elem_t)0;\n";
+      // Padding by a branch, or without one (clamped address, value zeroed afterwards).  A branch is cheaper where the loads behind
+      // it stay in flight together (f16 resnet stages in the declared order: 32x64x56x56 323 us, 366 without branches;
+      // 4x32x45x45, whose small maps split K, 59, 68).  Where K ends inside a tile there is a second test around it, and
+      // wavefronts that split K, one or two of them on a SIMD, wait for the loads one by one (residual blocks 3x96x74x10: f16
+      // 15.0, 13.3 us without either branch; f32 20.1, 17.4).
+      const bool branch = dot || WAVES_K == 1 || K % BK == 0;
+      if (!branch) k << "#define GATHER_NO_BRANCH 1\n";
+      if (branch) {
+        k << "  const idx_t a" << xh << " = g.h0 + kh_;\n";
+        k << "  const idx_t a" << xw << " = g.w0 + kw_;\n";
+        k << "  if (a" << xh << " < 0 || a" << xh << " >= " << H << " || a" << xw << " < 0 || a" << xw << " >= " << Wd << ") return (elem_t)0;\n";
+      } else {
+        k << "  const int h_ = g.h0 + kh_, w_ = g.w0 + kw_;\n";
+        k << "  const bool in_ = h_ >= 0 && h_ < " << H << " && w_ >= 0 && w_ < " << Wd << ";\n";
+        k << "  const idx_t a" << xh << " = min(max(h_, 0), " << H - 1 << "), a" << xw << " = min(max(w_, 0), " << Wd - 1 << ");\n";
+      }
       k << c.decl_parts(xatoms, "  ");
-      {
+      const ENode& xe = c.nodes[xnode];
+      if (xe.kind == ENode::LOAD && !xe.is_int && xe.addr.indirect.empty() && g.tensors[xe.tensor].dtype == X.dtype) {
+        // a stored element goes as it is: through float and back, bf16 values were waited for one by one (residual block
+        // 16x128x70x66 in bf16 228 us, 105 now; decoder half of a U-Net 8x256x16x16 in the declared order 425, 191)
+        k << "  const elem_t o = p" << pslot.at(xe.tensor) << "[" << c.addr_expr(xe.addr) << "];\n";
+      } else {
         std::set<int> done;
         c.emit_values(k, {xnode}, done, pslot, "  ");
+        k << "  elem_t o; cvt_out(&o, " << c.vname(xnode) << ");\n";
       }
-      k << "  elem_t o; cvt_out(&o, " << c.vname(xnode) << "); return o;\n}\n";
+      k << (branch ? "  return o;\n}\n" : "  return in_ ? o : (elem_t)0;\n}\n");
       k << "#define loadB_gather(Bb, kk, g) loadB_gather_impl(kk, g, KARGS_G)\n";
       if (direct) {
         // the operand value of (channel, tap) at a column, zero in the padding; tap is a constant after unrolling

@@ -617,7 +617,12 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #pragma unroll
     for (int i = 0; i < B_SC_N; ++i) {
       const int e = (WHOLE(BN * BK) || tid + i * NT < BN * BK) ? tid + i * NT : 0, r = e % BN, k = e / BN;
+#ifdef GATHER_NO_BRANCH
+      const elem_t v = loadB_gather(Bb, (FULL_K || k0 + k < GK ? (idx_t)(k0 + k) : (idx_t)(GK - 1)), gcol);
+      rb[s_][i] = (FULL_K || k0 + k < GK) ? v : (elem_t)0;
+#else
       rb[s_][i] = (FULL_K || k0 + k < GK) ? loadB_gather(Bb, k0 + k, gcol) : (elem_t)0;
+#endif
     }
 #else
 #pragma unroll

@@ -751,7 +751,7 @@ Lowered lower_conv(LowerCtx& c) {
     // a tuning build times all of them on the device instead (force_variant = 100 + index).
     auto nblocks = [&](int bm, int bn) { return ((GM + bm - 1) / bm) * ((GN + bn - 1) / bn); };
     int BK = eb == 2 ? (K <= 32 ? 32 : 64) : 16;
-    struct Tile { int BM, BN, WM, WN, WK, BK; bool direct = false; };
+    struct Tile { int BM, BN, WM, WN, WK, BK; bool direct = false; int nbuf = 0; };      // nbuf: buffers of the direct-to-LDS loop, 0: register-staged
     std::vector<Tile> tiles;
     // few output channels: a tile as tall as the channel count (four wavefronts side by side), so that a pixel's
     // channels are written by one workgroup as one contiguous run and no accumulator rows are staged for nothing
@@ -770,6 +770,37 @@ Lowered lower_conv(LowerCtx& c) {
     const size_t direct_idx = tiles.size() - 1;
     const size_t n_default = tiles.size();
 
+    // Operand tiles straight into LDS, several K tiles of loads in flight (see the MatMul template): 16-bit convolutions whose
+    // filter rows and operand pixels are both contiguous along K (channels-last, or pointwise on it), with nothing to run on the
+    // operand's values on their way.  A tap in the padding reads zeros.  Register-staged and this, us: 3x3 channels-last f16
+    // 32x64x56x56 -> 64 27.2, 16.2; 32x128x28x28 -> 128 22.0, 13.4; 8x256x32x32 -> 128 17.4, 13.9; 8x128x64x64 -> 64 13.5, 9.8;
+    // 8x64x128x128 -> 32 18.7, 11.7; 2x128x22x22 -> 64 7.2, 4.1.
+    const bool dma_ok = eb == 2 && amode == 0 && !dot && !prologue && (bmode == 4 || bmode == 0) && K >= 128 && !getenv("DNNF_CONV_NO_DMA");      // (developer switch for A/B runs)
+    size_t dma_pick = 0;
+    if (dma_ok) {
+      // Up to 704 tiles of 32x32: wavefronts split K, eight on tiles of 128 values where K is long and the chip is not full (2x128x22x22
+      // -> 64 w/ 62 tiles 4.1 us, four on 64 values 5.2), four otherwise (4x32x45x45 -> 32, 254 tiles, K 288: 3.0, 3.3; 64x64
+      // tiles 4.0).  Beyond, the form that the time model names (8x96x30x30 -> 96, 675 tiles of 32x32: 6.7 us, of 64x64 8.2;
+      // 8x256x32x32 -> 128, 1024 and 256 tiles: 14.9, 13.9), and 32x128 tiles where the map has no more than 32 channels.
+      const int64_t n32 = nblocks(32, 32), nk = (K + 63) / 64;
+      const size_t first = tiles.size();
+      tiles.push_back({32, 32, 1, 1, 4, 64, false, 4});
+      if (K >= 512) tiles.push_back({32, 32, 1, 1, 8, 128, false, 4});
+      dma_pick = K >= 512 && n32 <= 256 ? first + 1 : first;
+      if (GM <= 32) {
+        if (n32 > 704) dma_pick = tiles.size();
+        tiles.push_back({32, 128, 1, 4, 1, 64, false, 2});
+      } else {
+        double best = 1e30;
+        for (auto& d : dma_forms()) {
+          if (GM <= 64 && d.BM > 64) continue;
+          const double t = dma_time(d, (double)nblocks(d.BM, d.BN), nk);
+          if (n32 > 704 && t < best) { best = t; dma_pick = tiles.size(); }
+          tiles.push_back({d.BM, d.BN, d.WM, d.WN, 1, 64, false, d.NBUF});
+        }
+      }
+    }
+
     if (c.opts.force_variant >= 100) {
       DNNF_CHECK(!dot && c.opts.force_variant - 100 < (int)tiles.size(), DNNF_UNSUPPORTED_OP, "no such convolution tile variant");
       pick = (size_t)(c.opts.force_variant - 100);
@@ -778,18 +809,31 @@ Lowered lower_conv(LowerCtx& c) {
         if (tiles[i].WK == 1 && nblocks(tiles[i].BM, tiles[i].BN) >= 768) { pick = i; break; }
       if (tiles[pick].WK == 4 && nblocks(64, 64) >= 192) pick--;     // K-split tiles only for problems that cannot fill the chip otherwise
       if (tiles[pick].WK == 4 && direct_ok) pick = direct_idx;
+      if (dma_ok) pick = dma_pick;
     }
     const bool direct = tiles[pick].direct;
     int BM = tiles[pick].BM, BN = tiles[pick].BN, WAVES_M = tiles[pick].WM, WAVES_N = tiles[pick].WN, WAVES_K = tiles[pick].WK;
     BK = tiles[pick].BK;
     // a K-split kernel is a chain of dependent K steps: fewer, longer steps keep more loads in flight
     if (WAVES_K == 4 && eb == 4 && K >= 256) BK = 64;
+    int dma = tiles[pick].nbuf;
+    if (const char* e = getenv("DNNF_CONV_TILE")) {       // developer override for tuning runs: BM,BN,BK,WAVES_M,WAVES_N,WAVES_K,NBUF[,MIN_K]
+      int v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7) >= 7 && dma_ok && K >= v[7]) {
+        BM = v[0]; BN = v[1]; BK = v[2]; WAVES_M = v[3]; WAVES_N = v[4]; WAVES_K = v[5]; dma = v[6];
+      }
+    }
+    if (dma) {
+      const int vec = 16 / eb, nt = 64 * WAVES_M * WAVES_N * WAVES_K;
+      DNNF_CHECK((BM * BK / vec) % nt == 0 && (BN * BK / vec) % nt == 0 && dma >= 2 && dma <= 4, DNNF_UNSUPPORTED_OP, "tile does not divide into whole load passes");
+    }
     // the pointer the template calls PB is only dereferenced by the affine loaders
     k << "typedef " << c.ctype(X.dtype) << " elem_t;\n";
     k << "#define ELEM_BYTES " << eb << "\n#define BM " << BM << "\n#define BN " << BN << "\n#define BK " << BK << "\n";
     k << "#define GM " << GM << "\n#define GN " << GN << "\n#define GK " << K << "\n";
     k << "#define WAVES_M " << WAVES_M << "\n#define WAVES_N " << WAVES_N << "\n#define WAVES_K " << WAVES_K
-      << (K <= BK ? "\n#define NBUF 1\n#define PF 1\n" : "\n#define NBUF 2\n#define PF 2\n");   // a single K tile needs no second buffer
+      << (dma ? "\n#define DMA 1\n#define PF 1\n#define NBUF " + std::to_string(dma) + "\n" + gemm_kernel_zeros() :
+          K <= BK ? std::string("\n#define NBUF 1\n#define PF 1\n") : std::string("\n#define NBUF 2\n#define PF 2\n"));   // a single K tile needs no second buffer
     k << "#define A_MODE " << amode << "\n#define B_MODE " << bmode << "\n#define PA p" << wslot << "\n";
     {
       // the filter matrix was last read an inference ago: every XCD touches all of it up front (see the MatMul template)
@@ -889,6 +933,20 @@ Lowered lower_conv(LowerCtx& c) {
           << c.addr_expr(xaddr_t) << "));\n";
         k << "#pragma unroll\n  for (int e = 0; e < " << VEC << "; ++e) v[e] = in_ ? v[e] : 0;\n  return v;\n}\n";
         k << "#define loadB_tap(kk, g) loadB_tap_impl(kk, g, KARGS_G)\n";
+        if (dma) {
+          // the direct-to-LDS loop: a chunk is VEC channels of one tap of one pixel, addressed from the window's first tap; where a
+          // K tile lies inside one tap, the tap is the same for the whole workgroup
+          auto st = [&](int at) { auto it = xaddr_t.stride.find(at); return it == xaddr_t.stride.end() ? (int64_t)0 : it->second; };
+          const std::string px = "p" + std::to_string(pslot.at(c.nodes[xnode].tensor));
+          k << "DEV idx_t tap_base(const gcol_t g) { return g.n * (idx_t)" << st(xn) << " + g.h0 * (idx_t)" << st(xh) << " + g.w0 * (idx_t)" << st(xw) << " + (idx_t)" << xaddr_t.offset << "; }\n";
+          k << "DEV const void* tap_address_impl(idx_t k0, int kr, const gcol_t g, idx_t base, " << kparams << ") {\n";
+          if (C % BK == 0) k << "  const int tap = (int)(k0 / " << C << "), ch = (int)(k0 % " << C << ") + kr;\n";
+          else k << "  const int tap = (int)((k0 + kr) / " << C << "), ch = (int)((k0 + kr) % " << C << ");\n";
+          k << "  const int kh_ = tap / " << KW << ", kw_ = tap % " << KW << ", h_ = g.h0 + kh_, w_ = g.w0 + kw_;\n";
+          k << "  const bool in_ = h_ >= 0 && h_ < " << H << " && w_ >= 0 && w_ < " << Wd << ";\n";
+          k << "  return in_ ? (const void*)(" << px << " + (base + (kh_ * (idx_t)" << st(xh) << " + kw_ * (idx_t)" << st(xw) << " + ch))) : (const void*)dn_zeros;\n}\n";
+          k << "#define tap_address(k0, kr, g, base) tap_address_impl(k0, kr, g, base, KARGS_G)\n";
+        }
       }
     }
     k << gemm_epilogue_source(c, {}, rows, cols, pslot, kparams, GN, bslot, dot ? 0 : GM);
@@ -996,8 +1054,9 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
       Kn.grid[0] = (unsigned)nblocks(BM, BN);
       Kn.block[0] = (unsigned)(64 * WAVES_M * WAVES_N * WAVES_K);
       Lw.variant = direct ? "direct_32x32_taps" + std::to_string(KH * KW) + "_k4"
-                          : "igemm_" + std::to_string(BM) + "x" + std::to_string(BN) + "x" + std::to_string(BK) + "_a" + std::to_string(amode) + "b" + std::to_string(bmode) +
-                                (prologue ? "_pro" : "");
+                          : "igemm_" + std::to_string(BM) + "x" + std::to_string(BN) + "x" + std::to_string(BK) +
+                                (WAVES_M * WAVES_N * WAVES_K > 4 ? "_w" + std::to_string(WAVES_M * WAVES_N * WAVES_K) : std::string()) + (dma ? "_dma" + std::to_string(dma) : std::string()) +
+                                "_a" + std::to_string(amode) + "b" + std::to_string(bmode) + (prologue ? "_pro" : "");
     }
   }
   Lw.ext_in.assign(params.begin(), params.begin() + n_in);

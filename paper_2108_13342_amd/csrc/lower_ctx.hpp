@@ -143,7 +143,11 @@ void decl_digits(std::ostringstream& os, const LowerCtx& c, const std::vector<in
 // shared by the MatMul and Conv templates
 std::string gemm_offset_fn(const LowerCtx& c, const std::string& name, const std::vector<int>& atoms, const Affine& a);
 std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads);
+struct DmaForm { int BM, BN, WM, WN, NBUF; double t0, a0, a1, b; };
+const std::vector<DmaForm>& dma_forms();
+double dma_time(const DmaForm& f, double workgroups, int64_t nk);
 const char* gemm_kernel_body();
+const char* gemm_kernel_zeros();          // 16 bytes that direct-to-LDS loads read where an operand has none
 std::string gemm_epilogue_source(const LowerCtx& c, const std::vector<int>& batch, const std::vector<int>& rows,
                                  const std::vector<int>& cols, const std::map<int, int>& pslot, const std::string& kparams,
                                  int64_t GN, int row_bias_slot, int64_t GM = 0);   // GM > 0 allows the row-wise vector form

@@ -166,7 +166,6 @@ DEV void load_to_lds16(const void* g, const u32 lds) {
 DEV void load_to_lds4(const void* g, const u32 lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"((unsigned long long)g), "s"(lds) : "m0");
 }
-static __device__ __attribute__((aligned(16))) const u32 dn_zeros[4] = {0, 0, 0, 0};
 template <int N> struct int_c { static constexpr int v = N; };
 DEV u32 lds_address(void* p) { return __builtin_amdgcn_readfirstlane((u32)(unsigned long long)(__attribute__((address_space(3))) char*)p); }
 
@@ -279,12 +278,25 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
     ra_off[i] = offA_row(ROW_A(r));
     ra_k[i] = ((v % CPR) ^ SWZ(r)) * VEC;
   }
+#if B_MODE == 4
+  gcol_t rb_g[B_DIRECT_N];                               // channels-last convolution operand: rb_off is the window's first tap
+#endif
 #pragma unroll
   for (int i = 0; i < B_DIRECT_N; ++i) {
     const int v = tid + i * NT, r = v / CPR;
+#if B_MODE == 4
+    rb_g[i] = gather_col(COL_B(r));
+    rb_off[i] = tap_base(rb_g[i]);
+#else
     rb_off[i] = offB_col(COL_B(r));
+#endif
     rb_k[i] = ((v % CPR) ^ SWZ(r)) * VEC;
   }
+#if B_MODE == 4
+#define B_CHUNK(i, k0) tap_address(k0, rb_k[i], rb_g[i], rb_off[i])      // (a tap in the padding: the zeros)
+#else
+#define B_CHUNK(i, k0) (const void*)(Bb + rb_off[i] + offB_k((k0) + rb_k[i]))
+#endif
   auto dma_load = [&](const int buf, const idx_t k0) {
     const u32 la = lds_address((char*)&As[buf][0][0] + wave * 1024), lb = lds_address((char*)&Bs[buf][0][0] + wave * 1024);
 #pragma unroll
@@ -295,7 +307,7 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #pragma unroll
     for (int i = 0; i < B_DIRECT_N; ++i) {
       const idx_t k = k0 + rb_k[i];
-      load_to_lds16(FULL_K || k < GK ? (const void*)(Bb + rb_off[i] + offB_k(k)) : (const void*)dn_zeros, lb + i * NT * 16);
+      load_to_lds16(FULL_K || k < GK ? B_CHUNK(i, k0) : (const void*)dn_zeros, lb + i * NT * 16);
     }
   };
 #define LDS_WAIT() { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(0xC07F); __builtin_amdgcn_sched_barrier(0); }   /* lgkmcnt(0) */
@@ -970,6 +982,27 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 }  // namespace
 
 const char* gemm_kernel_body() { return kGemmBody; }
+const char* gemm_kernel_zeros() { return "static __device__ __attribute__((aligned(16))) const u32 dn_zeros[4] = {0, 0, 0, 0};\n"; }
+
+// Tile forms of the direct-to-LDS loop and their time model, us: t0 + the rounds of workgroups that the chip's compute units
+// hold at once, each nk * max(a0, r * a1) + b with r workgroups on a unit (a0: one alone, bound by its own chain of waits;
+// a1: the unit's share when it is full; b: first loads and epilogue).  128 bytes of K a row, so a 64x64 tile on three buffers
+// takes 48 KB of LDS (three workgroups on a compute unit), 128x128 on two 64 KB (two) and on three 96 KB (one).  Fitted to 35
+// products in bf16 (M 256 .. 8192, K 128 .. 3072, N 128 .. 3072, weights from beyond the L2 caches) on every form, 5 to 11 %
+// rms each; the form it names is 3 % slower than the best of them on average, where a model of matrix and LDS cycles was 16 %
+// slower, and up to 1.7 times (2048x1536x384 15.1 against 8.9).
+const std::vector<DmaForm>& dma_forms() {
+  static const std::vector<DmaForm> forms = {
+      {64, 64, 2, 2, 2, 1.81, 0.352, 0.225, 0.81},  {64, 64, 2, 2, 3, 1.53, 0.260, 0.214, 1.13},   {64, 64, 2, 2, 4, 1.69, 0.255, 0.210, 0.98},
+      {64, 128, 2, 4, 3, 1.00, 0.324, 0.326, 1.90}, {128, 64, 4, 2, 3, 1.14, 0.301, 0.319, 1.78},  {128, 128, 2, 4, 2, 1.00, 0.541, 0.612, 1.98},
+      {128, 128, 2, 4, 3, 1.00, 0.499, 0.300, 2.39}, {256, 128, 4, 2, 3, 1.00, 0.667, 0.891, 3.33}, {256, 256, 4, 2, 2, 1.00, 1.290, 1.398, 4.54}};
+  return forms;
+}
+double dma_time(const DmaForm& f, double workgroups, int64_t nk) {
+  const int lds = f.NBUF * (f.BM + f.BN) * 128 + 512, occ = std::min((160 << 10) / lds, 32 / (f.WM * f.WN));
+  const double n = workgroups / 256.0, full = std::floor(n / occ), rest = std::ceil(n - full * occ);
+  return f.t0 + full * ((double)nk * std::max(f.a0, occ * f.a1) + f.b) + (rest > 0 ? (double)nk * std::max(f.a0, rest * f.a1) + f.b : 0.0);
+}
 
 // The macros that make a kernel touch its weight operand up front (see touch_weights in the kernel): `lines` 128-byte lines
 // of parameter `slot`, `rows`: the left operand.  W_PF_N covers the largest share of any XCD, up to what the wait counts hold.
@@ -1360,41 +1393,13 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   }
   // both operands contiguous along K and K a whole number of tiles: tiles loaded straight into LDS
   const bool dma_ok = eb == 2 && amode == 0 && bmode == 0 && K % 64 == 0 && !getenv("DNNF_GEMM_NO_DMA");   // (developer switch for A/B runs)
-  // Time model of the direct-to-LDS forms, us: t0 + the rounds of workgroups that the chip's compute units hold at once,
-  // each nk * max(a0, r * a1) + b with r workgroups on a unit (a0: one alone, bound by its own chain of waits; a1: the unit's
-  // share when it is full; b: first loads and epilogue).  Fitted to 35 products (M 256 .. 8192, K 128 .. 3072, N 128 .. 3072,
-  // weights from beyond the L2 caches) on every form, 5 to 12 % rms each; the form it names is 3 % slower than the best of
-  // the nine on average, where the cycle model below was 16 %, and 67 % at worst (512x128x128 and larger tiles for few tiles
-  // of a long K: 2048x1536x384 15.1 against 8.9).
-  struct Fit { double t0, a0, a1, b; };
-  std::vector<Fit> fits(cands.size());
-  if (dma_ok) {
-    // tile, wavefronts, buffers: 128 bytes of K a row, so a 64x64 tile on three buffers takes 48 KB of LDS (three workgroups on
-    // a compute unit), 128x128 on two 64 KB (two) and on three 96 KB (one)
-    auto add = [&](int bm, int bn, int wm, int wn, int nbuf, Fit fit) { cands.push_back({bm, bn, 64, wm, wn, 1, nbuf, 1, 1}); fits.push_back(fit); };
-    add(64, 64, 2, 2, 2, {1.81, 0.352, 0.225, 0.81});
-    add(64, 64, 2, 2, 3, {1.53, 0.260, 0.214, 1.13});
-    add(64, 64, 2, 2, 4, {1.69, 0.255, 0.210, 0.98});
-    add(64, 128, 2, 4, 3, {1.00, 0.324, 0.326, 1.90});
-    add(128, 64, 4, 2, 3, {1.14, 0.301, 0.319, 1.78});
-    add(128, 128, 2, 4, 2, {1.00, 0.541, 0.612, 1.98});
-    add(128, 128, 2, 4, 3, {1.00, 0.499, 0.300, 2.39});
-    add(256, 128, 4, 2, 3, {1.00, 0.667, 0.891, 3.33});
-    add(256, 256, 4, 2, 2, {1.00, 1.290, 1.398, 4.54});
-  }
+  if (dma_ok) for (auto& d : dma_forms()) cands.push_back({d.BM, d.BN, 64, d.WM, d.WN, 1, d.NBUF, 1, 1});
   // Default choice: a cost model in cycles per CU.  A K tile costs the larger of its MFMA time and its
   // LDS time (16-byte fragment reads at 128 B/clk, stores at 64 B/clk) plus a fixed barrier/latency
   // share; tiles are dealt to 256 CUs, and partly filled rounds count in full.
   auto cost = [&](size_t ci) {
     const Cfg& f = cands[ci];
-    if (dma_ok) {
-      if (!f.DMA) return 1e30;
-      const Fit& m = fits[ci];
-      const int lds = f.NBUF * (f.BM + f.BN) * 128 + 512, occ = std::min((160 << 10) / lds, 32 / (f.WM * f.WN));
-      const double nkt = (double)(K / 64), n = (double)nblocks(f.BM, f.BN) / 256.0;
-      const double full = std::floor(n / occ), rest = std::ceil(n - full * occ);
-      return m.t0 + full * (nkt * std::max(m.a0, occ * m.a1) + m.b) + (rest > 0 ? nkt * std::max(m.a0, rest * m.a1) + m.b : 0.0);
-    }
+    if (dma_ok) return f.DMA ? dma_time(dma_forms()[ci - (cands.size() - dma_forms().size())], (double)nblocks(f.BM, f.BN), K / 64) : 1e30;
     const double tm = f.BM / f.WM / 32.0, tn = f.BN / f.WN / 32.0, steps = f.BK / 16.0;
     const double mfma = tm * tn * steps * (eb == 2 ? 32.0 : 512.0) * (f.WM * f.WN / 4.0);   // wavefronts share 4 SIMDs
     const double lds_rd = f.WM * f.WN * (tm + tn) * steps * 8.0;
@@ -1535,7 +1540,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   if (DMA) {
     const int vec = 16 / eb, nt = 64 * WAVES_M * WAVES_N * WAVES_K;
     DNNF_CHECK((BM * BK / vec) % nt == 0 && (BN * BK / vec) % nt == 0, DNNF_UNSUPPORTED_OP, "tile does not divide into whole load passes");
-    DNNF_CHECK(amode == 0 && bmode == 0 && (WAVES_K > 1 || (eb == 2 && K % BK == 0)) && NBUF >= 2 && NBUF <= 4, DNNF_UNSUPPORTED_OP, "operands cannot be loaded straight into LDS");
+    DNNF_CHECK(amode == 0 && bmode == 0 && (WAVES_K > 1 || eb == 2) && NBUF >= 2 && NBUF <= 4, DNNF_UNSUPPORTED_OP, "operands cannot be loaded straight into LDS");
   }
 
   // parameters: A, B, epilogue loads, outputs
@@ -1594,7 +1599,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   k << "#define GM " << GM << "\n#define GN " << GN << "\n#define GK " << K << "\n";
   k << "#define WAVES_M " << WAVES_M << "\n#define WAVES_N " << WAVES_N << "\n#define WAVES_K " << WAVES_K << "\n#define NBUF " << NBUF << "\n#define PF " << PF << "\n";
   k << "#define A_MODE " << amode << "\n#define B_MODE " << bmode << "\n#define PA p0\n#define PB p1\n";
-  if (DMA) k << "#define DMA 1\n";
+  if (DMA) k << "#define DMA 1\n" << gemm_kernel_zeros();
   {
     // a weight operand of up to 16 MB that the block reads whole (dense, no batch): touched by every XCD up front
     const Tensor& TBt = g.tensors[tb];

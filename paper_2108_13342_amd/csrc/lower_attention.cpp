@@ -80,7 +80,8 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
   u16x2 rv[V_SUB][8];
 #endif
 #define KEY(j) ((SK % BJ == 0) ? (idx_t)(j) : ((j) < SK ? (idx_t)(j) : (idx_t)(SK - 1)))
-#define KEY4(j) ((SK % BJ == 0) ? (idx_t)(j) : ((j) < SK ? (idx_t)(j) : (idx_t)(SK - 4)))   // start of a group of 4 keys
+// start of a group of 4 keys (SK no multiple of 4: the score operators clamp key by key)
+#define KEY4(j) ((SK % BJ == 0) ? (idx_t)(j) : ((j) < SK ? (idx_t)(j) : (idx_t)(SK % 4 == 0 ? SK - 4 : SK - 1)))
   auto gload = [&](const idx_t j0) {
 #if K_MODE == 0
     // keys stored [key][d], d contiguous: one 16-byte vector per (key, d-octet)
@@ -367,7 +368,10 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
   const int64_t SQ = fs.GM, SK = fs.GN, DH = fs.K, DV = fo.GN, GZ = fs.GZ;
   DNNF_CHECK(fo.GM == SQ && fo.K == SK && fo.GZ == GZ, DNNF_UNSUPPORTED_OP, "the two MatMul operators do not share rows / batch");
   DNNF_CHECK(DH % 16 == 0 && DH <= 128 && DV % 32 == 0 && DV <= 128, DNNF_UNSUPPORTED_OP, "head dimension outside the template's range");
-  DNNF_CHECK(SK % 8 == 0, DNNF_UNSUPPORTED_OP, "key count must be a multiple of 8");
+  // any number of keys where keys and values are read row by row (one row of head channels a key); an operand contiguous along
+  // the keys is read in vectors of eight
+  DNNF_CHECK(SK % 8 == 0 || (fs.bmode == 0 && fo.bmode == 1 && fs.cols.size() == 1 && fo.katoms.size() == 1), DNNF_UNSUPPORTED_OP,
+             "key count must be a multiple of 8");
   // the same (batch, query) numbering on both sides
   auto extents = [](const LowerCtx& c, const std::vector<int>& v) {
     std::vector<int64_t> e;
@@ -394,7 +398,7 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
   DNNF_CHECK(fs.bmode == 0 || fs.bmode == 1, DNNF_UNSUPPORTED_OP, "keys need a vectorisable layout");
   DNNF_CHECK(fo.bmode == 0 || fo.bmode == 1, DNNF_UNSUPPORTED_OP, "values need a vectorisable layout");
   const int inner = fs.cols.back();
-  DNNF_CHECK(cs.atom_extent[inner] % 4 == 0, DNNF_UNSUPPORTED_OP, "key axis split too finely");
+  DNNF_CHECK(SK % 8 != 0 || cs.atom_extent[inner] % 4 == 0, DNNF_UNSUPPORTED_OP, "key axis split too finely");
 
   // ---- parameters: Q, K, V, what the score operators read, what the epilogue reads, outputs
   std::vector<int> params = {fs.ta, fs.tb, fo.tb};
@@ -453,7 +457,7 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
       const ENode& e = cs.nodes[n];
       if (e.kind != ENode::LOAD || e.is_int) continue;
       Affine a = cs.resolved(e.addr);
-      bool contig = stride_of(a, inner) == 1 && a.offset % 4 == 0;
+      bool contig = stride_of(a, inner) == 1 && a.offset % 4 == 0 && SK % 4 == 0;
       for (auto& kv : a.stride) if (kv.first != inner && kv.second % 4) contig = false;
       if (!contig) continue;
       vloads.push_back(n);
@@ -482,7 +486,8 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
     decl_digits(k, cs, fs.cols, "cc", "  ", "qc");
     k << "  const idx_t inner0 = a" << inner << ";\n";
     k << "#pragma unroll\n  for (int u = 0; u < 4; ++u) {\n";
-    k << "    const idx_t a" << inner << " = inner0 + u;\n    const float anchor_v = s[u];\n";
+    k << "    const idx_t a" << inner << " = " << (SK % 4 == 0 ? std::string("inner0 + u") : "min((idx_t)(inner0 + u), (idx_t)" + std::to_string(SK - 1) + ")")
+      << ";\n    const float anchor_v = s[u];\n";
     std::set<int> done;
     cs.emit_values(k, {cs.stores[0].value}, done, pslot, "    ", &ov);
     k << "    s[u] = " << cs.vname(cs.stores[0].value) << ";\n  }\n}\n";

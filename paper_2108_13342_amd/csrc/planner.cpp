@@ -282,14 +282,29 @@ struct Planner {
         std::sort(blk.ops.begin(), blk.ops.end(), [&](int a, int b) { return topo_pos[a] < topo_pos[b]; });
         blk.fused_type = DNNF_MANY_TO_MANY;
         blk.weight_only = false;
-        try {
-          LowerOpts lo;
-          lo.intra_block = o.intra_block;
-          lower_block(g, blk, lo);
-        } catch (const Error& e) {
-          say(std::string("attention block refused: ") + e.what());
-          continue;
+        // The block as it stands, and, where that is refused, with the index operators in front of the keys taken in one after
+        // the other: a key matrix handed over as its transpose can be read in vectors along the keys only if their number is a
+        // multiple of 8, the tensor it was transposed from row by row for any number.
+        bool formed = false;
+        int kt = g.ops[mm1].in[1];
+        for (int step = 0; step < 4 && !formed; step++) {
+          try {
+            LowerOpts lo;
+            lo.intra_block = o.intra_block;
+            lower_block(g, blk, lo);
+            formed = true;
+          } catch (const Error& e) {
+            if (step == 0) say(std::string("attention block refused: ") + e.what());
+            const Tensor& K = g.tensors[kt];
+            const int kp = K.producer;
+            if (kp < 0 || !eligible(kp) || K.kind != DNNF_INTERMEDIATE || K.consumers.size() != 1 || g.ops[kp].in.size() != 1 ||
+                (g.ops[kp].info->cls != OC_RESHAPE && g.ops[kp].info->cls != OC_TRANSPOSE)) break;
+            blk.ops.push_back(kp);
+            std::sort(blk.ops.begin(), blk.ops.end(), [&](int a, int b) { return topo_pos[a] < topo_pos[b]; });
+            kt = g.ops[kp].in[0];
+          }
         }
+        if (!formed) continue;
         int id = (int)members.size();
         members.push_back(blk.ops);
         for (int op : blk.ops) group[op] = id;

@@ -29,6 +29,27 @@ def test_attention_block(args, kw):
     assert len(blocks) == 1 and len([d for d in s.plan.describe() if not d["prepare_only"] and d["family"] != 5]) == 1, s.plan.describe()
 
 
+@pytest.mark.parametrize("args,kw", [
+    ((1, 2, 33, 33, 64), dict(dtype="bf16", mask="causal")),                     # one key past a half tile, mask rows of odd length
+    ((2, 2, 77, 77, 64), dict(dtype="f16", mask="add")),                         # 13 keys in the second tile
+    ((1, 3, 50, 3, 32), dict(dtype="f16", mask=None, merge_heads=False)),        # fewer keys than a vector of scores
+    ((1, 1, 130, 203, 128), dict(dtype="bf16", mask="add")),                     # more queries than a workgroup takes
+    ((2, 1, 20, 68, 64), dict(dtype="f16", mask="causal")),                      # a multiple of 4 that is none of 8: mask in vectors
+    ((1, 2, 7, 130, 64), dict(dtype="bf16", mask="add")),                        # a multiple of 2
+])
+def test_attention_block_any_number_of_keys(args, kw):
+    """Keys read row by row (the Transpose in front of them joins the block): any number of them."""
+    s, _ = check_against_oracle(U.attention_block(*args, kt_stored=False, **kw), attention=1)
+    blocks = _attention_blocks(s)
+    assert len(blocks) == 1 and len([d for d in s.plan.describe() if not d["prepare_only"] and d["family"] != 5]) == 1, s.plan.describe()
+
+
+def test_attention_keys_stored_transposed_need_vectors():
+    """K handed over as its transpose is read along the keys: a number that is no multiple of 8 stays three blocks."""
+    s, _ = check_against_oracle(U.attention_block(1, 2, 33, 33, 64), attention=1)
+    assert not _attention_blocks(s)
+
+
 def test_attention_off_by_default():
     """Without the option the table decides: Many-to-Many + Many-to-Many stays split."""
     from paper_2108_13342_amd import api

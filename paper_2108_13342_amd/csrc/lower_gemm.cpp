@@ -1112,7 +1112,6 @@ std::string gemm_epilogue_source(const LowerCtx& c, const std::vector<int>& batc
   bool stores_vectors = false;     // set by vector_form: some destination is written with vector stores
   auto vector_form = [&](const std::vector<int>& rows, const std::vector<int>& cols, int64_t GN, bool transposed) -> std::string {
   stores_vectors = false;
-  if (!c.rep_atoms.empty()) return "";       // replicated results leave element by element
   std::ostringstream k;
   const int inner = cols.empty() ? -1 : cols.back(), outer = cols.size() >= 2 ? cols[cols.size() - 2] : -1;
   // A group of VE consecutive columns normally lies inside the fastest column atom.  It may also run
@@ -1164,6 +1163,8 @@ std::string gemm_epilogue_source(const LowerCtx& c, const std::vector<int>& batc
   decl_digits(k, c, rows, "r", "  ", "qr");
   decl_digits(k, c, cols, "cc", "  ", "qc");      // atoms of the group's first column
   k << "  const idx_t inner0 = a" << inner << ";\n";
+  for (int ra : reps) k << "  for (idx_t a" << ra << " = 0; a" << ra << " < " << c.atom_extent[ra] << "; ++a" << ra << ")\n";      // (once per destination of a replicated result)
+  k << "  {\n";
   std::map<int, std::string> ov;
   for (int n : need) {
     const ENode& e = c.nodes[n];
@@ -1212,7 +1213,7 @@ std::string gemm_epilogue_source(const LowerCtx& c, const std::vector<int>& batc
     if (s.preds.empty()) k << "  " << st << "\n";
     else k << "  if (" << c.pred_expr(s.preds) << ") { " << st << " }\n";
   }
-  k << "}\n";
+  k << "  }\n}\n";
   return k.str();
   };
   std::string vf = vector_form(rows, cols, GN, false);

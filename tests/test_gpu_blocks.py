@@ -35,6 +35,14 @@ def test_reduce_block(kind, shape, axes, keep):
     check_against_oracle(U.reduce_block(kind, shape, axes, keep))
 
 
+@pytest.mark.parametrize("kind", ["ReduceMean", "ReduceMax"])
+@pytest.mark.parametrize("args", [(1, 16, 61, 59, 40, 1), (3, 8, 90, 91, 24, 1)])
+def test_reduce_block_split(kind, args):
+    """Partial results of many workgroups, in numbers that are no multiple of the threads that add them up."""
+    s, _ = check_against_oracle(U.conv_pair_block(*args, reduce=kind), layout=1)
+    assert any("_split" in d["kernel_name"] for d in s.plan.describe()), s.plan.describe()
+
+
 @pytest.mark.parametrize("shape,dtype", [((2, 6, 9, 9), "f32"), ((3, 40, 14, 14), "f16"), ((2, 5, 112, 112), "f16")])
 def test_gap_block(shape, dtype):
     check_against_oracle(U.gap_block(shape, dtype))

@@ -129,6 +129,21 @@ def linear_layernorm_block(M, K, N, dtype="bf16", batch=(), residual=True, keep_
     return b.finish()
 
 
+def conv_pair_block(N, C, H, W, CO, K, stride=1, dtype="f16", reduce=None, seed=41):
+    """A pointwise convolution with a Relu and behind it a K x K one with bias and Relu: with data formats selected, the
+    second reads a channels-last map (and a reduction of the result's positions behind it, reduce, such a one too)."""
+    st = _st(seed)
+    b = GraphBuilder("conv_pair_block", dtype)
+    x = b.input("x", (N, C, H, W), st.normal((N, C, H, W), 0.0, 1.0, dtype))
+    w0 = b.weight("w0", (C, C, 1, 1), st.normal((C, C, 1, 1), 0.0, math.sqrt(2.0 / C), dtype))
+    w1 = b.weight("w1", (CO, C, K, K), st.normal((CO, C, K, K), 0.0, math.sqrt(2.0 / (C * K * K)), dtype))
+    bs = b.weight("b1", (CO,), st.normal((CO,), 0.0, 0.2, dtype))
+    y = configs._un(b, "Relu", configs._conv(b, x, w0, None, 1, 0))
+    y = configs._un(b, "Relu", configs._conv(b, y, w1, bs, stride, K // 2))
+    b.mark_output(configs._reduce(b, reduce, y, [2, 3], 1) if reduce else y)
+    return b.finish()
+
+
 def se_tail_block(N, C, H, W, CR, dtype="f16", scale=True, bias=True, act="swish", seed=38, dw=None):
     """The squeeze-excite tail of a mobile-network block: GlobalAveragePool -> 1x1 Conv (C -> CR) -> swish (or Relu) ->
     1x1 Conv (CR -> C) -> Sigmoid [-> x * s].  H = W = 1: the first layer reads an already pooled vector.

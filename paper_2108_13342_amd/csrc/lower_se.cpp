@@ -21,7 +21,7 @@ const char* kSeBody = R"KRN(
 #define SE_WR (SE_CR / SE_EPW)                  // words per weight row
 #define SE_PW (SE_WR | 1)                       // row pitch of a wavefront's weight slice in LDS: odd, every row its own bank
 #define SE_JPW ((SE_CR + SE_NT / 64 - 1) / (SE_NT / 64))                 // hidden units per wavefront
-#define SE_CPW (((SE_CO + 63) / 64 + SE_NT / 64 - 1) / (SE_NT / 64))     // groups of 64 output rows per wavefront
+#define SE_CPW (((SE_CO + 63) / 64 + SE_SPLIT * SE_NT / 64 - 1) / (SE_SPLIT * SE_NT / 64))     // groups of 64 output rows per wavefront
 extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
   __shared__ float pooled[SE_C];
   __shared__ float hid[SE_CR];
@@ -30,7 +30,56 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
 #endif
   __shared__ unsigned int wt[SE_NT / 64][64 * SE_PW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const idx_t n = blockIdx.x;
+  const idx_t n = blockIdx.x / SE_SPLIT;
+  const int group0 = blockIdx.x % SE_SPLIT * (SE_NT / 64);            // this workgroup's first group of 64 output rows is wavefront 0's
+
+  // ---- both layers' weights, where they fit the registers: they depend on nothing, were last read an inference ago, and
+  // asked for layer by layer each costs a memory round trip of its own behind the one of the vector in front of it
+#ifdef SE_W1VEC
+#define SE_IT1 ((SE_C / SE_W1VEC + 63) / 64)
+#else
+#define SE_IT1 1000
+#endif
+#define SE_EARLY (SE_JPW * SE_IT1 * 4 + SE_CPW * SE_WR <= 160)
+#if SE_EARLY
+  typedef elem_t w1vec_t __attribute__((ext_vector_type(SE_W1VEC)));
+  w1vec_t w1reg[SE_JPW][SE_IT1];
+#pragma unroll
+  for (int q = 0; q < SE_JPW; ++q)
+#pragma unroll
+    for (int it = 0; it < SE_IT1; ++it) {
+      const int j = wave + q * (SE_NT / 64), cv = lane + it * 64;      // (past the end: the last row, the first vector - never used)
+      w1reg[q][it] = *(const w1vec_t*)(PW1 + (idx_t)(j < SE_CR ? j : SE_CR - 1) * SE_C + (cv < SE_C / SE_W1VEC ? cv : 0) * SE_W1VEC);
+    }
+#endif
+  float b1reg[(SE_JPW + 63) / 64], b2reg[SE_CPW];
+#pragma unroll
+  for (int q0 = 0; q0 < SE_JPW; q0 += 64) {
+    const int j = wave + (q0 + lane) * (SE_NT / 64);
+    b1reg[q0 / 64] = se_bias1(j < SE_CR ? j : 0, KARGS);
+  }
+#pragma unroll
+  for (int q = 0; q < SE_CPW; ++q) {
+    const int r = (group0 + wave + q * (SE_SPLIT * SE_NT / 64)) * 64 + lane;
+    b2reg[q] = se_bias2(r < SE_CO ? r : 0, KARGS);
+  }
+  unsigned int wreg[SE_CPW][SE_WR];
+  auto load_w2 = [&]() {
+#pragma unroll
+    for (int q = 0; q < SE_CPW; ++q) {
+      const int r0 = (group0 + wave + q * (SE_SPLIT * SE_NT / 64)) * 64;
+      const int nrows = r0 >= SE_CO ? 0 : (SE_CO - r0 < 64 ? SE_CO - r0 : 64);
+      const unsigned int* __restrict__ src = (const unsigned int*)(PW2 + (idx_t)(r0 < SE_CO ? r0 : 0) * SE_CR);
+#pragma unroll
+      for (int t = 0; t < SE_WR; ++t) {
+        const int i = lane + t * 64;
+        wreg[q][t] = src[i < nrows * SE_WR ? i : 0];                     // (past the end: a word that is never used)
+      }
+    }
+  };
+#if SE_EARLY
+  load_w2();
+#endif
 
   // ---- the pooled vector
 #if SE_HW == 1
@@ -77,7 +126,16 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
       s[q] = 0.0f;
       const int j = wave + q * (SE_NT / 64);
       if (j < SE_CR) {
-#ifdef SE_W1VEC
+#if SE_EARLY
+#pragma unroll
+        for (int it = 0; it < SE_IT1; ++it) {
+          const int cv = lane + it * 64;
+          if (cv < SE_C / SE_W1VEC) {
+#pragma unroll
+            for (int u = 0; u < SE_W1VEC; ++u) s[q] += pooled[cv * SE_W1VEC + u] * cvt_in(w1reg[q][it][u]);
+          }
+        }
+#elif defined(SE_W1VEC)
         typedef elem_t w1vec_t __attribute__((ext_vector_type(SE_W1VEC)));
 #pragma unroll
         for (int it = 0; it < (SE_C / SE_W1VEC + 63) / 64; ++it) {
@@ -94,11 +152,17 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
 #endif
       }
     }
+    // the units' operators run side by side, lane = unit: one after the other in lane 0 each would wait for its operands
 #pragma unroll
-    for (int q = 0; q < SE_JPW; ++q) {
-      const int j = wave + q * (SE_NT / 64);
-      const float t = dn_wave_sum(s[q]);
-      if (j < SE_CR && lane == 0) hid[j] = se_mid(n, j, t, KARGS);
+    for (int q0 = 0; q0 < SE_JPW; q0 += 64) {
+      float t = 0.0f;
+#pragma unroll
+      for (int q = q0; q < (q0 + 64 < SE_JPW ? q0 + 64 : SE_JPW); ++q) {
+        const float v = dn_wave_sum(s[q]);
+        if (lane == q - q0) t = v;
+      }
+      const int j = wave + (q0 + lane) * (SE_NT / 64);
+      if (q0 + lane < SE_JPW && j < SE_CR) hid[j] = se_mid(n, j, t + b1reg[q0 / 64], KARGS);
     }
   }
   __syncthreads();
@@ -108,21 +172,12 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
   // and copied into its own LDS slice, then lane = row walks its row; the slice belongs to the wavefront alone,
   // whose LDS operations complete in order, so no barrier is involved.
   {
-    unsigned int wreg[SE_CPW][SE_WR];
+#if !SE_EARLY
+    load_w2();
+#endif
 #pragma unroll
     for (int q = 0; q < SE_CPW; ++q) {
-      const int r0 = (wave + q * (SE_NT / 64)) * 64;
-      const int nrows = r0 >= SE_CO ? 0 : (SE_CO - r0 < 64 ? SE_CO - r0 : 64);
-      const unsigned int* __restrict__ src = (const unsigned int*)(PW2 + (idx_t)(r0 < SE_CO ? r0 : 0) * SE_CR);
-#pragma unroll
-      for (int t = 0; t < SE_WR; ++t) {
-        const int i = lane + t * 64;
-        wreg[q][t] = i < nrows * SE_WR ? src[i] : 0u;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < SE_CPW; ++q) {
-      const int r0 = (wave + q * (SE_NT / 64)) * 64;
+      const int r0 = (group0 + wave + q * (SE_SPLIT * SE_NT / 64)) * 64;
       const int nrows = r0 >= SE_CO ? 0 : (SE_CO - r0 < 64 ? SE_CO - r0 : 64);
 #pragma unroll
       for (int t = 0; t < SE_WR; ++t) {
@@ -144,7 +199,7 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
           s += hid[w] * __builtin_bit_cast(float, word);
 #endif
         }
-        se_out(n, r0 + lane, s, KARGS);
+        se_out(n, r0 + lane, s + b2reg[q], KARGS);
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -360,6 +415,14 @@ Lowered lower_squeeze_excite(const Graph& g, const Block& b, const LowerOpts& o)
   k << "typedef " << (wide ? "long long" : "int") << " idx_t;\n";
   k << "typedef " << k1.ctype(dtype) << " elem_t;\n";
   k << "#define ELEM_BYTES " << eb << "\n#define SE_C " << C << "\n#define SE_CR " << CR << "\n#define SE_CO " << CO << "\n#define SE_HW " << HW << "\n";
+  // An image's second layer is shared among as many workgroups as have a group of 64 rows for each of their eight wavefronts, while
+  // the images leave compute units idle; each computes the first layer for itself (a pool in front is too much to repeat).  The
+  // kernel is a chain of memory round trips and one compute unit's LDS traffic.  32 images, 1152 x 48 x 1152, us: weights fetched
+  // layer by layer, units' operators one after the other 14.3; both layers' weights and biases up front, operators side by side
+  // 8.2; three workgroups an image 5.6.  672 x 28 x 672: 9.4, 5.0, 4.1 with two.
+  int split = 1;
+  if (gap < 0) while (N * (split + 1) <= 256 && (int64_t)split * 512 < CO) split++;
+  k << "#define SE_SPLIT " << split << "\n";
   if (V) k << "#define SE_VEC " << V << "\n#define SE_G " << G << "\n";
   if (C % (16 / eb) == 0) k << "#define SE_W1VEC " << 16 / eb << "\n";
   k << "#define PW1 p" << w1 << "\n#define PW2 p" << w2 << "\n";
@@ -381,11 +444,12 @@ Lowered lower_squeeze_excite(const Graph& g, const Block& b, const LowerOpts& o)
     k << "  const xvec_t xv = *(const xvec_t*)(p" << pslot.at(kp.nodes[xnode].tensor) << " + (" << kp.addr_expr(kp.nodes[xnode].addr) << "));\n";
     k << "#pragma unroll\n  for (int u = 0; u < " << V << "; ++u) v[u] = cvt_in(xv[u]);\n}\n";
   }
+  k << "DEV float se_bias1(idx_t j, " << kparams << ") { return " << (bs1 >= 0 ? "cvt_in(p" + std::to_string(bs1) + "[j])" : "0.0f") << "; }\n";
+  k << "DEV float se_bias2(idx_t c, " << kparams << ") { return " << (bs2 >= 0 ? "cvt_in(p" + std::to_string(bs2) + "[c])" : "0.0f") << "; }\n";
   // first layer's result -> the second layer's operand, as the separate kernel would have stored it
   k << "DEV float se_mid(idx_t n, idx_t j, float anchor_v, " << kparams << ") {\n";
   decl_digits(k, k1, f1.n_atoms, "n", "  ", "qn");
   decl_digits(k, k1, f1.c_atoms, "j", "  ", "qj");
-  if (bs1 >= 0) k << "  anchor_v += cvt_in(p" << bs1 << "[j]);\n";
   {
     std::set<int> done;
     k1.emit_values(k, {k1.stores[0].value}, done, pslot, "  ");
@@ -395,7 +459,6 @@ Lowered lower_squeeze_excite(const Graph& g, const Block& b, const LowerOpts& o)
   k << "DEV void se_out(idx_t n, idx_t c, float anchor_v, " << kparams << ") {\n";
   decl_digits(k, k2, f2.n_atoms, "n", "  ", "qn");
   decl_digits(k, k2, f2.c_atoms, "c", "  ", "qc");
-  if (bs2 >= 0) k << "  anchor_v += cvt_in(p" << bs2 << "[c]);\n";
   {
     std::set<int> done;
     std::vector<int> roots;
@@ -417,7 +480,7 @@ Lowered lower_squeeze_excite(const Graph& g, const Block& b, const LowerOpts& o)
   Lw.ext_out.assign(params.begin() + n_in, params.end());
   Launch Kn;
   Kn.params = params;
-  Kn.grid[0] = (unsigned)N;
+  Kn.grid[0] = (unsigned)(N * split);
   Kn.block[0] = 512;
   std::string src = std::string(device_preamble()) + k.str();
   Kn.name = fnv_name("dnnf_se", src);

@@ -259,6 +259,17 @@ def test_pool_inside_the_depthwise_convolution(args, kw, variant):
     check_against_oracle(spec, squeeze_excite=1, profile=1, layout=1)
 
 
+@pytest.mark.parametrize("args,kw", [
+    ((3, 1040, 1, 1, 44), dict(scale=False)),                                    # three workgroups an image; the last row group has 16 rows
+    ((2, 700, 1, 1, 30), dict(scale=False, dtype="bf16")),                       # first layer's rows in no vectors
+    ((1, 516, 1, 1, 22), dict(scale=False, dtype="f32", bias=False)),            # the second workgroup has 4 rows
+    ((130, 528, 1, 1, 6), dict(scale=False)),                                    # images enough: one workgroup each
+])
+def test_squeeze_excite_second_layer_shared_among_workgroups(args, kw):
+    s, _ = check_against_oracle(U.se_tail_block(*args, **kw), squeeze_excite=2)
+    assert 7 in _families(s), s.plan.describe()
+
+
 def test_squeeze_excite_tail_leaves_large_maps_their_pooling_kernel():
     s, _ = check_against_oracle(U.se_tail_block(2, 32, 40, 40, 8), squeeze_excite=2, layout=1)
     fams = _families(s)

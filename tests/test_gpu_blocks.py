@@ -363,6 +363,22 @@ def test_conv_block(args, kw):
     assert _families(s) == [3], s.plan.describe()
 
 
+@pytest.mark.parametrize("args,kw,variant", [
+    ((2, 48, 43, 41, 40, 3), dict(), "32x32x64_dma4"),                           # K of 432: its last tile is three quarters full
+    ((1, 96, 47, 46, 33, 3), dict(), "32x32x128_w8_dma4"),                       # eight wavefronts split K; one output channel past a tile
+    ((2, 40, 31, 29, 64, 3), dict(stride=2, dtype="bf16"), "32x32x64_dma4"),     # taps of 40 channels straddle the K tiles
+    ((2, 16, 107, 106, 24, 3), dict(dtype="bf16"), "32x128x64_dma2"),            # K of 144; few output channels
+    ((1, 24, 130, 131, 72, 3), dict(), "_dma"),                                  # tiles without K split, ragged both ways
+    ((1, 136, 20, 19, 72, 1), dict(), "32x32x64_dma4"),                          # pointwise
+])
+def test_conv_direct_to_lds(args, kw, variant):
+    """16-bit convolutions on channels-last maps load straight into LDS: K that ends inside a tile, maps that end inside a
+    tile, padding on every side."""
+    s, _ = check_against_oracle(U.conv_pair_block(*args, **kw), layout=1)
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if not d["prepare_only"]]
+    assert any(variant in x and "_dma" in x for x in names), names
+
+
 def test_conv_variants_chosen():
     """The shapes above reach the loaders they are meant to exercise."""
     def variant(*args, **kw):

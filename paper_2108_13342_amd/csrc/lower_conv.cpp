@@ -691,9 +691,8 @@ Lowered lower_conv(LowerCtx& c) {
     // A convolution with few outputs (the squeeze-and-excitation layers: 1x1 spatial, batch x channels
     // results) is a handful of dot products: one wavefront per output element, lanes striding over K,
     // finishes in one memory round trip where a tiled GEMM would walk K tile by tile in one workgroup.
-    const bool dot = GM * GN <= 65536 && GM * GN * K <= ((int64_t)8 << 20) && c.rep_atoms.empty();
+    bool dot = GM * GN <= 65536 && GM * GN * K <= ((int64_t)8 << 20) && c.rep_atoms.empty();
     int bcvec = 0;
-    if (dot) pointwise = false;
     Affine ab;
     if (pointwise) {
       // x[n, ci, p, q] with ci = k: substitute the conv-input atoms by output / k atoms
@@ -728,10 +727,13 @@ Lowered lower_conv(LowerCtx& c) {
       // without vectors along the pixels the gathering loader (lanes along pixels) coalesces better
       // than the generic scalar one (lanes along K)
       if (kdirect) { bmode = 0; bcvec = 0; }
-      else if (bcvec && !prologue) bmode = 1;
-      else { bmode = 3; pointwise = false; }        // (a prologue is generated for K-contiguous vectors only)
+      else if (bcvec && !prologue && !dot) bmode = 1;
+      else { bmode = 3; bcvec = 0; pointwise = false; }        // (a prologue is generated for K-contiguous vectors only)
     }
     if (!pointwise) prologue = false;
+    // ... but not where the direct-to-LDS tiles take it and there are tiles enough: 480x14x14 -> 80 4.1 us, 3.2 tiled;
+    // 240x28x28 -> 40 3.9, 3.0; 144x28x28 -> 40 3.8, 2.8; at 672x7x7 -> 192 they are level (4.1).
+    if (dot && bmode == 0 && eb == 2 && !prologue && K >= 128 && GM >= 32 && GN >= 64) dot = false;
     // Filters re-laid [co, kh, kw, ci] by data-format selection: K runs tap by tap.  With a stored channels-last
     // operand every K vector is VEC channels of one tap (tap loader, B_MODE 4); any other operand is gathered
     // element by element in the same K order.
@@ -1003,7 +1005,51 @@ Lowered lower_conv(LowerCtx& c) {
       k << "  return __builtin_bit_cast(" << (eb == 2 ? "u16x8" : "f32x4") << ", ov);\n}\n";
     }
     Lw.family = FAM_CONV;
-    if (dot) {
+    if (dot && bmode == 0) {
+      // Both operands contiguous along K (a stored map with its channels last, a 1x1 map in any order): 16-byte vectors of both,
+      // as many lanes to an output element as a row has vectors, 64 at most, so that a row's loads are in flight together; K short
+      // of a wavefront shares it among neighbouring output channels, whose filter rows are neighbours in memory.  Bound by latency, us, f16, one
+      // element a lane and step and this: 1152x1x1 -> 48 8.3, 2.6; 672x1x1 -> 28 5.5, 2.6; 480x14x14 -> 80 10.1, 4.1.
+      const int nv = (int)(K / VEC);
+      int lpo = 1;
+      while (lpo < 64 && lpo < nv) lpo *= 2;
+      k << "#define LPO " << lpo << "\n#define NVEC " << nv << "\n";
+      k << R"KRN(
+extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
+  constexpr int VE = 16 / ELEM_BYTES;
+  typedef elem_t dvec_t __attribute__((ext_vector_type(VE)));
+  const int lane = threadIdx.x % LPO;
+  const idx_t o0 = (idx_t)blockIdx.x * (256 / LPO) + threadIdx.x / LPO;
+  const idx_t o = o0 < (idx_t)GM * GN ? o0 : (idx_t)GM * GN - 1;
+  const idx_t r = o % GM, cc = o / GM;
+  const elem_t* __restrict__ ap = PA + offA_batch(0) + offA_row(r);
+  const elem_t* __restrict__ bp = PB + offB_batch(0) + offB_col(cc);      // (the batch offset holds the operand's constant part)
+  float colv[NCOLV > 0 ? NCOLV : 1];
+  col_loads(cc, colv, KARGS);
+  float acc = 0.0f;
+#pragma unroll 8
+  for (int it = 0; it < (NVEC + LPO - 1) / LPO; ++it) {
+    const int v = lane + it * LPO;
+    const bool in = NVEC % LPO == 0 || v < NVEC;
+    const idx_t kk = (in ? v : 0) * VE;                    // (past the end: the first vector, not added)
+    const dvec_t a = *(const dvec_t*)(ap + kk);
+    dvec_t b = *(const dvec_t*)(bp + kk);
+#ifdef B_PROLOGUE
+    b = __builtin_bit_cast(dvec_t, b_prologue(__builtin_bit_cast(vec_t, b), cc, kk, KARGS));
+#endif
+    float p = 0.0f;
+#pragma unroll
+    for (int u = 0; u < VE; ++u) p += cvt_in(a[u]) * cvt_in(b[u]);
+    acc += in ? p : 0.0f;
+  }
+#pragma unroll
+  for (int d = LPO / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);
+  if (lane == 0 && o0 == o) epilogue(0, r, cc, acc, colv, KARGS);
+}
+)KRN";
+      Kn.grid[0] = (unsigned)((GM * GN + 256 / lpo - 1) / (256 / lpo));
+      Lw.variant = std::string(K <= 64 ? "dot_lane_k" : "dot_wave_k") + std::to_string(K) + "_v" + std::to_string(VEC);
+    } else if (dot) {
       k << R"KRN(
 extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
   const int lane = threadIdx.x & 63;

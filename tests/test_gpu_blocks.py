@@ -379,6 +379,19 @@ def test_conv_direct_to_lds(args, kw, variant):
     assert any(variant in x and "_dma" in x for x in names), names
 
 
+@pytest.mark.parametrize("args,kw,variant", [
+    ((2, 200, 9, 9, 24, 1), dict(), "dot_wave_k200_v8"),                         # 25 vectors on 32 lanes
+    ((1, 1160, 5, 5, 9, 1), dict(dtype="bf16"), "dot_wave_k1160_v8"),            # 145 vectors on a wavefront
+    ((1, 48, 6, 5, 70, 1), dict(), "dot_lane_k48_v8"),                           # 6 vectors on 8 lanes, 32 outputs a workgroup
+    ((3, 8, 3, 3, 5, 1), dict(), "dot_lane_k8_v8"),                              # a vector is a whole row
+    ((1, 20, 6, 6, 9, 1), dict(dtype="f32"), "dot_lane_k20_v4"),
+])
+def test_conv_few_outputs_by_vectors(args, kw, variant):
+    s, _ = check_against_oracle(U.conv_pair_block(*args, **kw), layout=1)
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if not d["prepare_only"]]
+    assert variant in names, names
+
+
 def test_conv_variants_chosen():
     """The shapes above reach the loaders they are meant to exercise."""
     def variant(*args, **kw):

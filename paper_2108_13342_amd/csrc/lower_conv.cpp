@@ -256,7 +256,11 @@ Lowered lower_conv(LowerCtx& c) {
             if (HO % th == 0) { ldsTH = th; break; }
       }
     }
-    bool use_lds = ldsTH > 0 && (c.opts.force_variant >= 101 || (c.opts.force_variant < 100 && KH * KW > 9));
+    // ... but where its workgroups leave half the chip idle, more and smaller ones that read the map directly are done first: a
+    // staged one spends 4 to 7 us whatever their number (5x5, f16: 480x14x14, 15 workgroups, 6.8 us, direct 3.5; 144x56x56 at
+    // stride 2, 40 workgroups, 5.7, 3.6; 1152x7x7 4.6, 3.4).
+    const bool few = VC && ldsTH > 0 && N * ((C / VC + ldsXC - 1) / ldsXC) * (HO / ldsTH) * (WO / ldsTW) < 128;
+    bool use_lds = ldsTH > 0 && (c.opts.force_variant >= 101 || (c.opts.force_variant < 100 && KH * KW > 9 && !few));
     if (pool_dst >= 0) {
       // one workgroup must see every pixel of an image for its channels: the staged kernel with the whole plane as its patch
       DNNF_CHECK(VC && ldsTH == HO && ldsTW == WO && c.opts.force_variant != 100, DNNF_UNSUPPORTED_OP,

@@ -270,6 +270,14 @@ def test_squeeze_excite_second_layer_shared_among_workgroups(args, kw):
     assert 7 in _families(s), s.plan.describe()
 
 
+@pytest.mark.parametrize("n,variant", [(3, "dw_chan"), (70, "dw_lds")])
+def test_depthwise_kernel_by_number_of_workgroups(n, variant):
+    """5x5 on channels-last maps: staged from 128 workgroups on, the direct kernel below."""
+    s, _ = check_against_oracle(U.se_tail_block(n, 64, 14, 14, 16, dw=(5, 1)), layout=1)
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if not d["prepare_only"]]
+    assert any(x.startswith(variant) for x in names), names
+
+
 def test_squeeze_excite_tail_leaves_large_maps_their_pooling_kernel():
     s, _ = check_against_oracle(U.se_tail_block(2, 32, 40, 40, 8), squeeze_excite=2, layout=1)
     fams = _families(s)

@@ -1022,6 +1022,11 @@ Lowered lower_conv(LowerCtx& c) {
 extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
   constexpr int VE = 16 / ELEM_BYTES;
   typedef elem_t dvec_t __attribute__((ext_vector_type(VE)));
+#if ELEM_BYTES == 2
+  typedef u16x8 raw_t;                                     // (the form in which b_prologue takes a vector)
+#else
+  typedef f32x4 raw_t;
+#endif
   const int lane = threadIdx.x % LPO;
   const idx_t o0 = (idx_t)blockIdx.x * (256 / LPO) + threadIdx.x / LPO;
   const idx_t o = o0 < (idx_t)GM * GN ? o0 : (idx_t)GM * GN - 1;
@@ -1039,7 +1044,7 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
     const dvec_t a = *(const dvec_t*)(ap + kk);
     dvec_t b = *(const dvec_t*)(bp + kk);
 #ifdef B_PROLOGUE
-    b = __builtin_bit_cast(dvec_t, b_prologue(__builtin_bit_cast(vec_t, b), cc, kk, KARGS));
+    b = __builtin_bit_cast(dvec_t, b_prologue(__builtin_bit_cast(raw_t, b), cc, kk, KARGS));
 #endif
     float p = 0.0f;
 #pragma unroll
@@ -1052,7 +1057,7 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
 }
 )KRN";
       Kn.grid[0] = (unsigned)((GM * GN + 256 / lpo - 1) / (256 / lpo));
-      Lw.variant = std::string(K <= 64 ? "dot_lane_k" : "dot_wave_k") + std::to_string(K) + "_v" + std::to_string(VEC);
+      Lw.variant = std::string(K <= 64 ? "dot_lane_k" : "dot_wave_k") + std::to_string(K) + "_v" + std::to_string(VEC) + (prologue ? "_front" : "");      // (not _pro: that name is the planner's word for the tiles' prologue)
     } else if (dot) {
       k << R"KRN(
 extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import unit_graphs as U
+from test_host_convs import FRONTS
 from parity import check_against_oracle
 
 pytestmark = pytest.mark.gpu
@@ -398,6 +399,13 @@ def test_conv_few_outputs_by_vectors(args, kw, variant):
     s, _ = check_against_oracle(U.conv_pair_block(*args, **kw), layout=1)
     names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if not d["prepare_only"]]
     assert variant in names, names
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("front,args,kw", FRONTS)
+def test_conv_few_outputs_with_operators_in_front(front, args, kw, dtype):
+    s, _ = check_against_oracle(U.front_conv_block(front, *args, dtype=dtype, **kw), layout=1)
+    assert any(d["kernel_name"].endswith("_front") for d in s.plan.describe()), s.plan.describe()
 
 
 def test_conv_variants_chosen():

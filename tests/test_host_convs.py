@@ -1,0 +1,38 @@
+"""Kernels of convolutions compile, whatever stands in front of their operand; no device needed."""
+import os
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+import unit_graphs as U
+from paper_2108_13342_amd import api
+
+
+FRONTS = [                                                   # (what stands in front, shape, ...): K on its lanes, in 16 bits
+    ("Relu", (2, 16, 1, 1, 8), {}),                          # 2 vectors on 2 lanes
+    ("Relu", (2, 24, 8, 8, 16), dict(keep=True)),            # 3 on 4, a channels-last map
+    ("Relu", (1, 1160, 1, 1, 9), {}),                     # 145 on a wavefront
+    ("Relu", (3, 104, 3, 5, 24), dict(keep=True)),           # 13 on 16
+]
+
+
+def _kernels(spec, **kw):
+    g, _ = api.graph_from_spec(spec)
+    g.rewrite()
+    plan = api.Plan(g, [1] * len(spec.weights()), **kw)
+    return [d["kernel_name"].split(":")[1] for d in plan.describe() if not d["prepare_only"]]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("front,args,kw", FRONTS)
+def test_operators_in_front_of_a_convolution_of_few_results(front, args, kw, dtype, tmp_path):
+    spec = U.front_conv_block(front, *args, dtype=dtype, **kw)
+    assert any(k.startswith("dot_") and k.endswith("_front") for k in _kernels(spec, layout=1)), _kernels(spec, layout=1)
+    assert api.precompile_spec(spec, cache_dir=str(tmp_path), layout=1) > 0
+    assert api.precompile_spec(spec, cache_dir=str(tmp_path), layout=0) > 0
+
+
+@pytest.mark.parametrize("seed", [139, 231, 380])
+def test_random_networks_with_operators_in_front(seed, tmp_path):
+    assert api.precompile_spec(U.random_cnn(seed, "f16", n_ops=10 + seed % 7), cache_dir=str(tmp_path), layout=1) > 0

@@ -144,6 +144,29 @@ def conv_pair_block(N, C, H, W, CO, K, stride=1, dtype="f16", reduce=None, seed=
     return b.finish()
 
 
+def front_conv_block(front, N, C, H, W, CO, dtype="f16", keep=False, seed=43):
+    """A One-to-One operator in front of a pointwise convolution with bias (Cast: the input is stored in another float type).  keep: a per-channel scale in front of it that a 3 x 3 convolution
+    reads, too, and a Sigmoid behind the pointwise one: the operator joins the convolution and not the scale."""
+    st = _st(seed)
+    b = GraphBuilder("front_conv_block", dtype)
+    other = {"f16": "f32", "bf16": "f32", "f32": "f16"}[dtype]
+    x = b.input("x", (N, C, H, W), st.normal((N, C, H, W), 0.0, 1.0, other if front == "Cast" else dtype), dtype=other if front == "Cast" else dtype)
+    w = b.weight("w", (CO, C, 1, 1), st.normal((CO, C, 1, 1), 0.0, math.sqrt(2.0 / C), dtype))
+    bs = b.weight("b", (CO,), st.normal((CO,), 0.0, 0.2, dtype))
+    if keep:
+        x = configs._bin(b, "Mul", x, b.weight("sc", (1, C, 1, 1), st.normal((1, C, 1, 1), 1.0, 0.3, dtype)))
+    if front == "Cast":
+        y = configs._cast(b, x, dtype)
+    else:
+        y = configs._un(b, front, x)
+    y = configs._conv(b, y, w, bs, 1, 0)
+    b.mark_output(configs._un(b, "Sigmoid", y) if keep else y)
+    if keep:
+        w4 = b.weight("w4", (C, C, 3, 3), st.normal((C, C, 3, 3), 0.0, math.sqrt(2.0 / (9 * C)), dtype))
+        b.mark_output(configs._conv(b, x, w4, None, 1, 1))
+    return b.finish()
+
+
 def se_tail_block(N, C, H, W, CR, dtype="f16", scale=True, bias=True, act="swish", seed=38, dw=None):
     """The squeeze-excite tail of a mobile-network block: GlobalAveragePool -> 1x1 Conv (C -> CR) -> swish (or Relu) ->
     1x1 Conv (CR -> C) -> Sigmoid [-> x * s].  H = W = 1: the first layer reads an already pooled vector.

@@ -666,7 +666,8 @@ Lowered lower_conv(LowerCtx& c) {
     // those operators then run on the loaded vectors on their way into LDS (operand prologue).
     int main_load = -1;
     bool prologue = false;
-    if (c.nodes[xnode].kind == ENode::LOAD) main_load = xnode;
+    // (a load of another type - a Cast in front, folded into it - is converted element by element by the gathering loader)
+    if (c.nodes[xnode].kind == ENode::LOAD) main_load = !c.nodes[xnode].is_int && g.tensors[c.nodes[xnode].tensor].dtype == X.dtype ? xnode : -1;
     else if (c.nodes[xnode].kind == ENode::OP) {
       std::set<int> seen;
       std::vector<int> stack = {xnode};

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import unit_graphs as U
-from test_host_convs import FRONTS
+from test_host_convs import CASTS, FRONTS
 from parity import check_against_oracle
 
 pytestmark = pytest.mark.gpu
@@ -406,6 +406,13 @@ def test_conv_few_outputs_by_vectors(args, kw, variant):
 def test_conv_few_outputs_with_operators_in_front(front, args, kw, dtype):
     s, _ = check_against_oracle(U.front_conv_block(front, *args, dtype=dtype, **kw), layout=1)
     assert any(d["kernel_name"].endswith("_front") for d in s.plan.describe()), s.plan.describe()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("args", CASTS)
+def test_pointwise_operand_stored_in_another_type(args, dtype):
+    s, _ = check_against_oracle(U.front_conv_block("Cast", *args, dtype=dtype), rewrite=dtype != "f32")
+    assert _families(s) == [3], s.plan.describe()
 
 
 def test_conv_variants_chosen():

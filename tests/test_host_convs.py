@@ -33,6 +33,18 @@ def test_operators_in_front_of_a_convolution_of_few_results(front, args, kw, dty
     assert api.precompile_spec(spec, cache_dir=str(tmp_path), layout=0) > 0
 
 
+CASTS = [(2, 16, 1, 1, 8), (70, 256, 1, 1, 24), (300, 256, 1, 1, 64), (8, 64, 16, 16, 48)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("args", CASTS)
+def test_pointwise_operand_stored_in_another_type(args, dtype, tmp_path):
+    """A Cast that becomes part of the load: the vector paths read the convolution's own type only."""
+    spec = U.front_conv_block("Cast", *args, dtype=dtype)
+    for layout in (0, 1):
+        assert api.precompile_spec(spec, cache_dir=str(tmp_path), layout=layout, rewrite=dtype != "f32") > 0      # (a widening Cast is rewritten away)
+
+
 @pytest.mark.parametrize("seed", [139, 231, 380])
 def test_random_networks_with_operators_in_front(seed, tmp_path):
     assert api.precompile_spec(U.random_cnn(seed, "f16", n_ops=10 + seed % 7), cache_dir=str(tmp_path), layout=1) > 0

@@ -40,7 +40,7 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
 #else
 #define SE_IT1 1000
 #endif
-#define SE_EARLY (SE_JPW * SE_IT1 * 4 + SE_CPW * SE_WR <= 160)
+#define SE_EARLY (SE_ALONE && SE_JPW * SE_IT1 * 4 + SE_CPW * SE_WR <= 160)
 #if SE_EARLY
   typedef elem_t w1vec_t __attribute__((ext_vector_type(SE_W1VEC)));
   w1vec_t w1reg[SE_JPW][SE_IT1];
@@ -53,16 +53,18 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
     }
 #endif
   float b1reg[(SE_JPW + 63) / 64], b2reg[SE_CPW];
+  auto load_biases = [&]() {
 #pragma unroll
-  for (int q0 = 0; q0 < SE_JPW; q0 += 64) {
-    const int j = wave + (q0 + lane) * (SE_NT / 64);
-    b1reg[q0 / 64] = se_bias1(j < SE_CR ? j : 0, KARGS);
-  }
+    for (int q0 = 0; q0 < SE_JPW; q0 += 64) {
+      const int j = wave + (q0 + lane) * (SE_NT / 64);
+      b1reg[q0 / 64] = se_bias1(j < SE_CR ? j : 0, KARGS);
+    }
 #pragma unroll
-  for (int q = 0; q < SE_CPW; ++q) {
-    const int r = (group0 + wave + q * (SE_SPLIT * SE_NT / 64)) * 64 + lane;
-    b2reg[q] = se_bias2(r < SE_CO ? r : 0, KARGS);
-  }
+    for (int q = 0; q < SE_CPW; ++q) {
+      const int r = (group0 + wave + q * (SE_SPLIT * SE_NT / 64)) * 64 + lane;
+      b2reg[q] = se_bias2(r < SE_CO ? r : 0, KARGS);
+    }
+  };
   unsigned int wreg[SE_CPW][SE_WR];
   auto load_w2 = [&]() {
 #pragma unroll
@@ -78,6 +80,7 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
     }
   };
 #if SE_EARLY
+  load_biases();
   load_w2();
 #endif
 
@@ -115,6 +118,9 @@ extern "C" __global__ __launch_bounds__(SE_NT) void KNAME(KPARAMS) {
   }
 #endif
   __syncthreads();
+#if !SE_EARLY
+  load_biases();
+#endif
 
   // ---- first layer: one wavefront per hidden unit, lanes along the channels.  A wavefront's units are walked with
   // compile-time bounds and separate sums, so that every weight load of the layer is issued before the first reduction
@@ -423,6 +429,10 @@ Lowered lower_squeeze_excite(const Graph& g, const Block& b, const LowerOpts& o)
   int split = 1;
   if (gap < 0) while (N * (split + 1) <= 256 && (int64_t)split * 512 < CO) split++;
   k << "#define SE_SPLIT " << split << "\n";
+  // Weights up front take the registers that a second workgroup on the compute unit would live in (300 and 1024 images, f16,
+  // 1152 x 46 x 1152, us: up front 15.0, 28.8, layer by layer 10.3, 19.5), and in f32 those that a pool in front has its loads in
+  // flight with (32 maps 480x14x14, 20 hidden: 10.8, 6.8): only while no compute unit gets two workgroups, and not there.
+  k << "#define SE_ALONE " << (N * split <= 256 && (gap < 0 || eb == 2) ? 1 : 0) << "\n";
   if (V) k << "#define SE_VEC " << V << "\n#define SE_G " << G << "\n";
   if (C % (16 / eb) == 0) k << "#define SE_W1VEC " << 16 / eb << "\n";
   k << "#define PW1 p" << w1 << "\n#define PW2 p" << w2 << "\n";

@@ -1,0 +1,33 @@
+"""Rules that choose between forms of a kernel, read from the generated source without a device."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+import unit_graphs as U
+from paper_2108_13342_amd import api
+from workloads import configs
+from workloads.graph import GraphBuilder
+
+
+def _sources(spec, rewrite=True, **kw):
+    """(kernel name, source) of every block that runs per inference."""
+    g, _ = api.graph_from_spec(spec)
+    if rewrite:
+        g.rewrite()
+    plan = api.Plan(g, [1] * len(spec.weights()), **kw)
+    return [(d["kernel_name"].split(":")[1], plan.block_source(i)) for i, d in enumerate(plan.describe()) if not d["prepare_only"] and d["family"] != 5]
+
+
+@pytest.mark.parametrize("args,kw,early", [
+    ((85, 1040, 1, 1, 44), dict(scale=False), 1),                       # 255 workgroups, three an image
+    ((256, 96, 1, 1, 8), dict(scale=False), 1),
+    ((257, 96, 1, 1, 8), dict(scale=False), 0),                         # a compute unit gets two workgroups
+    ((4, 96, 7, 7, 8), dict(scale=False), 1),                           # a pool in front, 16 bits
+    ((4, 96, 7, 7, 8), dict(scale=False, dtype="f32"), 0),              # a pool in front, f32
+])
+def test_squeeze_excite_weights_up_front(args, kw, early):
+    src = [s for n, s in _sources(U.se_tail_block(*args, **kw), squeeze_excite=2) if "fc" in n]
+    assert len(src) == 1 and f"#define SE_ALONE {early}\n" in src[0]

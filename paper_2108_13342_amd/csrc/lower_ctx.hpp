@@ -142,7 +142,7 @@ void decl_digits(std::ostringstream& os, const LowerCtx& c, const std::vector<in
 
 // shared by the MatMul and Conv templates
 std::string gemm_offset_fn(const LowerCtx& c, const std::string& name, const std::vector<int>& atoms, const Affine& a);
-std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads);
+std::string weight_touch_macros(int64_t lines, int slot, bool rows, bool whole, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads);
 struct DmaForm { int BM, BN, WM, WN, NBUF; double t0, a0, a1, b; };
 const std::vector<DmaForm>& dma_forms();
 double dma_time(const DmaForm& f, double workgroups, int64_t nk);

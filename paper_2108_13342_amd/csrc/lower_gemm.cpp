@@ -209,14 +209,20 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // every workgroup's loop would wait for a memory round trip of its own.  Instead the workgroups of each XCD touch
   // what their tiles will read of the matrix between them (one 4-byte load per 128-byte line, landing in a spare piece
   // of LDS that nobody reads), so all of it is on its way into that XCD's L2 while the first tiles are being loaded.
-  // The tiles of an XCD are consecutive: inside one group of tile-rows they cover a run of columns, otherwise all.
+  // The tiles of an XCD are consecutive: inside one group of tile-rows they cover a run of columns, otherwise all.  Where
+  // the operand's rows of K do not lie one behind the other (a weight stored [K][N]), a run of columns is no run of lines
+  // and all of them are touched (W_PF_WHOLE).
   // In the direct-to-LDS loop every wavefront issues W_PF_N loads (lanes past its share touch the last line again): they are
   // counted there.
   auto touch_weights = [&]() {
     const idx_t nb = tiles_m * tiles_n, x = blockIdx.x % 8, nx = nb / 8 + (x < nb % 8 ? 1 : 0);
     const idx_t t0 = bid - blockIdx.x / 8, t1 = t0 + nx - 1;
     const bool one = t0 / grp == t1 / grp;
-#ifdef W_PF_ROWS
+#if defined(W_PF_WHOLE)
+    const idx_t lo = 0;
+    const bool to_end = true;
+    const idx_t hi = GN;
+#elif defined(W_PF_ROWS)
     // (a filter matrix is the left operand: the tile-rows of the group, or, inside one column, those from tile to tile)
     const bool column = one && (t0 % grp) / gsz == (t1 % grp) / gsz;
     const idx_t lo = one ? (g0 + (column ? (t0 % grp) % gsz : 0)) * BM : 0, hi = one ? (g0 + (column ? (t1 % grp) % gsz + 1 : gsz)) * BM : GM;
@@ -226,17 +232,17 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
     const bool to_end = hi >= GN;
 #endif
     const idx_t l0 = (idx_t)((long long)lo * GK * ELEM_BYTES / 128), l1 = to_end ? (idx_t)W_PREFETCH_LINES : (idx_t)((long long)hi * GK * ELEM_BYTES / 128);
-    const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
     const idx_t per = (l1 - l0 + nx - 1) / nx, first = l0 + (blockIdx.x / 8) * per, end = first + per < l1 ? first + per : l1;
+    const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
+#ifdef DMA
 #pragma unroll
     for (int i = 0; i < W_PF_N; ++i) {
       const idx_t line = first + tid + i * NT;
-#ifdef DMA
       load_to_lds4((const char*)W_PREFETCH_PTR + (long long)(line < end ? line : l1 - 1) * 128, spare);
-#else
-      if (line < end) load_to_lds4((const char*)W_PREFETCH_PTR + (long long)line * 128, spare);
-#endif
     }
+#else
+    for (idx_t line = first + tid; line < end; line += NT) load_to_lds4((const char*)W_PREFETCH_PTR + (long long)line * 128, spare);
+#endif
   };
 #else
 #define W_PF_N 0
@@ -1005,8 +1011,9 @@ double dma_time(const DmaForm& f, double workgroups, int64_t nk) {
 }
 
 // The macros that make a kernel touch its weight operand up front (see touch_weights in the kernel): `lines` 128-byte lines
-// of parameter `slot`, `rows`: the left operand.  W_PF_N covers the largest share of any XCD, up to what the wait counts hold.
-std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads) {
+// of parameter `slot`, `rows`: the left operand, `whole`: its rows of K are not one behind the other.  W_PF_N, the number of
+// touches a lane of the direct-to-LDS loop issues, covers the largest share of any XCD, up to what the wait counts hold.
+std::string weight_touch_macros(int64_t lines, int slot, bool rows, bool whole, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads) {
   const int64_t nb = tiles_m * tiles_n, grp = 8 * tiles_n;
   int64_t most = 1;
   for (int64_t x = 0, t0 = 0; x < 8; x++) {
@@ -1014,7 +1021,7 @@ std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tile
     if (!nx) continue;
     const int64_t t1 = t0 + nx - 1, g0 = t0 / grp * 8, gsz = std::min<int64_t>(8, tiles_m - g0);
     int64_t lo = 0, hi = rows ? GM : GN;
-    if (t0 / grp == t1 / grp) {
+    if (t0 / grp == t1 / grp && !whole) {
       const int64_t c0 = (t0 % grp) / gsz, c1 = (t1 % grp) / gsz;
       if (!rows) { lo = c0 * BN; hi = (c1 + 1) * BN; }
       else { lo = (g0 + (c0 == c1 ? (t0 % grp) % gsz : 0)) * BM; hi = (g0 + (c0 == c1 ? (t1 % grp) % gsz + 1 : gsz)) * BM; }
@@ -1025,7 +1032,8 @@ std::string weight_touch_macros(int64_t lines, int slot, bool rows, int64_t tile
   }
   std::ostringstream k;
   k << "#define W_PREFETCH_LINES " << lines << "\n#define W_PREFETCH_PTR p" << slot << "\n#define W_PF_N " << std::min<int64_t>(most, 24) << "\n";
-  if (rows) k << "#define W_PF_ROWS 1\n";
+  if (whole) k << "#define W_PF_WHOLE 1\n";
+  else if (rows) k << "#define W_PF_ROWS 1\n";
   return k.str();
 }
 
@@ -1606,8 +1614,13 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     const Tensor& TBt = g.tensors[tb];
     const int64_t wbytes = TBt.n() * dtype_bytes(TBt.dtype);
     if (!norm && GZ == 1 && (TBt.kind == DNNF_WEIGHT || TBt.weight_only) && wbytes >= (256 << 10) && wbytes <= ((int64_t)16 << 20) &&
-        wbytes == GN * K * eb && !getenv("DNNF_NO_WEIGHT_PREFETCH"))      // (developer switch for A/B runs)
-      k << weight_touch_macros(wbytes / 128, 1, false, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K * eb, 64 * WAVES_M * WAVES_N * WAVES_K);
+        wbytes == GN * K * eb && !getenv("DNNF_NO_WEIGHT_PREFETCH")) {    // (developer switch for A/B runs)
+      int64_t next = 1;                  // [N][K]: K innermost, then the columns in their own order
+      bool by_rows = true;
+      for (auto* atoms : {&katoms, &cols})
+        for (auto it = atoms->rbegin(); it != atoms->rend(); ++it) { by_rows = by_rows && stride_of(ab, *it) == next; next *= c.atom_extent[*it]; }
+      k << weight_touch_macros(wbytes / 128, 1, false, !by_rows, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K * eb, 64 * WAVES_M * WAVES_N * WAVES_K);
+    }
   }
   if (TA.dtype == DNNF_F16) k << "typedef f16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_f16\n";
   else if (TA.dtype == DNNF_BF16) k << "typedef bf16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_bf16\n";

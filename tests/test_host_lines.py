@@ -31,3 +31,15 @@ def _sources(spec, rewrite=True, **kw):
 def test_squeeze_excite_weights_up_front(args, kw, early):
     src = [s for n, s in _sources(U.se_tail_block(*args, **kw), squeeze_excite=2) if "fc" in n]
     assert len(src) == 1 and f"#define SE_ALONE {early}\n" in src[0]
+
+
+@pytest.mark.parametrize("M,K,N,dtype,rewrite,whole", [
+    (64, 1024, 1024, "bf16", True, False),                              # stored [N][K] after rewriting
+    (64, 132, 1024, "bf16", True, True),                                # K no multiple of a vector: stays [K][N]
+    (64, 1024, 1024, "bf16", False, True),                              # not rewritten
+    (64, 1001, 1024, "f32", True, True),
+])
+def test_weight_touches_cover_what_the_tiles_read(M, K, N, dtype, rewrite, whole):
+    """A run of columns is a run of memory lines only where the weight's rows of K lie one behind the other."""
+    src = _sources(U.gemm_block(M, K, N, dtype), rewrite)[0][1]
+    assert "#define W_PREFETCH_LINES" in src and ("#define W_PF_WHOLE 1" in src) == whole

@@ -17,6 +17,7 @@
 // The generated score function applies the block's One-to-One operators (scaling, masks) to four
 // consecutive keys at a time; the generated epilogue is the GEMM template's (LDS-staged, vector stores).
 #include <algorithm>
+#include <cmath>
 #include <set>
 #include <sstream>
 
@@ -422,6 +423,20 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
   std::set<int> need_s, need_o;
   collect(cs, need_s);
   collect(co, need_o);
+  // A workgroup walks all keys for its 128 queries; the separate kernels spread keys over the chip as well.  Key counts that only
+  // this template's row-by-row reads made possible form a block up to 256 keys, and beyond where its time is well below theirs.
+  // Both estimates (us) are fitted to 1117 blocks, bf16, 1 .. 192 heads, 1 .. 4001 queries, 9 .. 4001 keys, head sizes 32 .. 128,
+  // with no, an additive and a truth-value mask (16 and 13 % rms).  Separate and block, us, additive
+  // mask: 12 heads 1x1025 23.5, 32.0; 16 heads of 128, 100x770 25.8, 36.2; 16 heads of 128, 1x4001 88, 147 (these stay apart);
+  // 12 heads 1025x1025 60.6, 44.2; 48 heads 513x513 68.5, 26.0; 192 heads 300x385 114, 44.
+  if (SK % 8 != 0 && SK > 256) {
+    bool masked = false;
+    for (int n : need_s) masked = masked || (cs.nodes[n].kind == ENode::LOAD && stride_of(cs.resolved(cs.nodes[n].addr), inner) != 0);
+    const double keys = (double)SK, scores = (double)GZ * SQ * SK, workgroups = (double)(GZ * ((SQ + 127) / 128));
+    const double block = 4.0 + std::ceil(keys / 64) * (0.65 + 0.0098 * DH + (masked ? 0.75 : 0.0)) * (1.0 + 0.45 * workgroups / 256);
+    const double apart = 12.6 + 0.0136 * keys + scores * (3.4e-6 + 0.8e-8 * DH) + 0.6e-6 * GZ * keys * DH;
+    DNNF_CHECK(block <= 0.85 * apart, DNNF_UNSUPPORTED_OP, "separate kernels are faster for so many keys and so few queries");
+  }
   size_t n_in = params.size();
   for (auto& s : co.stores) {
     DNNF_CHECK(!pslot.count(s.tensor) && s.tensor != fs.ta && s.tensor != fs.tb && s.tensor != fo.tb, DNNF_UNSUPPORTED_OP,
@@ -453,18 +468,23 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
     // vector, so that the kernel can issue the loads of the next key tile a whole step ahead.
     std::map<int, std::string> ov;
     std::vector<int> vloads;
+    std::set<int> anywhere;            // of these, the ones whose groups of four start at any element
     for (int n : need_s) {
       const ENode& e = cs.nodes[n];
-      if (e.kind != ENode::LOAD || e.is_int) continue;
+      if (e.kind != ENode::LOAD || (e.is_int && g.tensors[e.tensor].dtype != DNNF_BOOL)) continue;
       Affine a = cs.resolved(e.addr);
-      bool contig = stride_of(a, inner) == 1 && a.offset % 4 == 0 && SK % 4 == 0;
+      bool contig = stride_of(a, inner) == 1 && a.offset % 4 == 0 && SK % 4 == 0 && !e.is_int;
       for (auto& kv : a.stride) if (kv.first != inner && kv.second % 4) contig = false;
-      if (!contig) continue;
+      // rows of a number of keys that is no multiple of 8 start at any element: the same four keys, by an unaligned load (bf16, four
+      // heads of 32, 300 queries, 1025 keys, us: element by element where they are used 75, four at a time a step ahead 34)
+      if (!contig && (SK % 8 == 0 || SK < 4 || stride_of(a, inner) != 1)) continue;
+      if (!contig) anywhere.insert(n);
       vloads.push_back(n);
-      ov[n] = "cvt_in(L.lv" + std::to_string(n) + "[u])";
+      ov[n] = (e.is_int ? "(float)L.lv" : "cvt_in(L.lv") + std::to_string(n) + (e.is_int ? "[u]" : "[u])");
     }
     for (int n : vloads)
-      k << "typedef " << cs.ctype(g.tensors[cs.nodes[n].tensor].dtype) << " lv" << n << "_t __attribute__((ext_vector_type(4)));\n";
+      k << "typedef " << cs.ctype(g.tensors[cs.nodes[n].tensor].dtype) << " lv" << n << "_t __attribute__((ext_vector_type(4)"
+        << (anywhere.count(n) ? ", aligned(" + std::to_string(dtype_bytes(g.tensors[cs.nodes[n].tensor].dtype)) + ")" : std::string()) << "));\n";
     k << "struct sload_t {\n";
     for (int n : vloads) k << "  lv" << n << "_t lv" << n << ";\n";
     if (vloads.empty()) k << "  int none;\n";
@@ -474,9 +494,17 @@ Lowered lower_attention(const Graph& g, const Block& b, const LowerOpts& o) {
     decl_digits(k, cs, fs.rows, "r", "  ", "qr");
     decl_digits(k, cs, fs.cols, "cc", "  ", "qc");
     k << "  sload_t L;\n";
+    if (!anywhere.empty())             // (a group that ends behind the last key is read from the last four on, and moved down)
+      k << "  const idx_t first = min((idx_t)a" << inner << ", (idx_t)" << SK - 4 << ");\n  const int skip = (int)(a" << inner << " - first);\n";
     for (int n : vloads) {
       const ENode& e = cs.nodes[n];
-      k << "  L.lv" << n << " =*(const lv" << n << "_t*)(p" << pslot.at(e.tensor) << " + (" << cs.addr_expr(e.addr) << "));\n";
+      if (anywhere.count(n)) {
+        const std::string l = "L.lv" + std::to_string(n);
+        k << "  { const idx_t a" << inner << " = first; " << l << " = *(const lv" << n << "_t*)(p" << pslot.at(e.tensor) << " + (" << cs.addr_expr(e.addr) << ")); }\n";
+        if (SK % 4) k << "  if (skip & 1) " << l << " = " << l << ".yzww;\n  if (skip & 2) " << l << " = " << l << ".zwww;\n";
+      } else {
+        k << "  L.lv" << n << " =*(const lv" << n << "_t*)(p" << pslot.at(e.tensor) << " + (" << cs.addr_expr(e.addr) << "));\n";
+      }
     }
     if (vloads.empty()) k << "  L.none = 0;\n";
     k << "  return L;\n}\n";

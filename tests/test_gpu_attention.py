@@ -44,6 +44,18 @@ def test_attention_block_any_number_of_keys(args, kw):
     assert len(blocks) == 1 and len([d for d in s.plan.describe() if not d["prepare_only"] and d["family"] != 5]) == 1, s.plan.describe()
 
 
+@pytest.mark.parametrize("args,kw", [
+    ((1, 2, 70, 253, 64), dict(dtype="bf16", mask="causal")),                    # rows of odd length: groups of four start at any element
+    ((2, 1, 9, 131, 32), dict(dtype="f16", mask="where")),                       # truth values; three keys in the last group
+    ((1, 3, 64, 66, 64), dict(dtype="bf16", mask="where")),                      # two
+    ((1, 1, 33, 5, 32), dict(dtype="f16", mask="causal")),                       # one, behind one whole group
+    ((1, 2, 20, 140, 64), dict(dtype="f16", mask="where")),                      # a multiple of 4 that is none of 8
+])
+def test_attention_masks_of_any_row_length(args, kw):
+    s, _ = check_against_oracle(U.attention_block(*args, kt_stored=False, **kw), attention=1)
+    assert len(_attention_blocks(s)) == 1, s.plan.describe()
+
+
 def test_attention_keys_stored_transposed_need_vectors():
     """K handed over as its transpose is read along the keys: a number that is no multiple of 8 stays three blocks."""
     s, _ = check_against_oracle(U.attention_block(1, 2, 33, 33, 64), attention=1)

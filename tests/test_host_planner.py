@@ -237,6 +237,21 @@ def test_weight_layout_rewrite():
     assert sum(1 for b in blocks if b["family"] == 2) == 6
 
 
+@pytest.mark.parametrize("args,formed", [
+    ((1, 4, 1, 253, 64), 1), ((1, 4, 1, 333, 64), 1),        # up to 256 keys; a short walk
+    ((1, 12, 1, 1025, 64), 0), ((1, 12, 1, 1024, 64), 1),    # many keys, few queries: separate kernels; multiples of 8 are not asked
+    ((2, 8, 100, 770, 128), 0), ((12, 12, 260, 333, 64), 1),
+    ((1, 12, 300, 1025, 64), 1),
+])
+def test_attention_block_of_any_number_of_keys_where_it_pays(args, formed):
+    import sys, os
+    sys.path.insert(0, os.path.dirname(__file__))
+    import unit_graphs as U
+
+    _, _, blocks = _plan(U.attention_block(*args, dtype="bf16", mask=None, kt_stored=False), rewrite=True, attention=1)
+    assert (6 in [b["family"] for b in blocks]) == bool(formed), blocks
+
+
 def test_attention_block_is_an_option_beyond_the_table():
     """MatMul - Div - Add - Softmax - MatMul: the table keeps the three Many-to-Many operators apart (red
     cells); with the extension switched on they and the head-merging Transpose / Reshape form one block."""

@@ -218,6 +218,9 @@ def attention_block(B, H, SQ, SK, D, dtype="f16", mask="add", kt_stored=True, me
     elif mask == "causal":
         m = np.triu(np.full((SQ, SK), -1e4), k=1 + SK - SQ).reshape(1, 1, SQ, SK)
         s = configs._bin(b, "Add", s, b.weight("mask", (1, 1, SQ, SK), rng.round_to(m, dtype)))
+    elif mask == "where":      # truth values, False on the masked keys
+        keep = st.uniform((1, 1, SQ, SK), 0.0, 1.0, "f32") < 0.8
+        s = b.op("Where", [b.weight("keep", (1, 1, SQ, SK), keep, dtype="bool"), s, b.const("low", -1e4)], (B, H, SQ, SK))
     p = b.op("Softmax", [s], (B, H, SQ, SK), {"axis": -1})
     o = configs._matmul(b, p, v)
     if merge_heads:

@@ -848,7 +848,7 @@ Lowered lower_conv(LowerCtx& c) {
       const char* e = getenv("DNNF_CONV_PREFETCH_KB");       // (developer switch for A/B runs: smallest filter, 0 = never)
       const int64_t min_kb = e ? atoll(e) : 64;
       if (!dot && !direct && min_kb > 0 && wbytes >= (min_kb << 10) && wbytes <= ((int64_t)16 << 20) && wbytes % 128 == 0)
-        k << weight_touch_macros(wbytes / 128, wslot, true, false, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K * eb, 64 * WAVES_M * WAVES_N * WAVES_K);
+        k << weight_touch_macros(wbytes / 128, wslot, TOUCH_ROWS, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K, eb, 64 * WAVES_M * WAVES_N * WAVES_K);
     }
     if (bcvec) k << "#define B_CVEC " << bcvec << "\n";
     if (direct) {

@@ -142,7 +142,8 @@ void decl_digits(std::ostringstream& os, const LowerCtx& c, const std::vector<in
 
 // shared by the MatMul and Conv templates
 std::string gemm_offset_fn(const LowerCtx& c, const std::string& name, const std::vector<int>& atoms, const Affine& a);
-std::string weight_touch_macros(int64_t lines, int slot, bool rows, bool whole, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads);
+enum TouchOrder { TOUCH_COLS, TOUCH_ROWS, TOUCH_STRIP, TOUCH_WHOLE };      // right operand [N][K], left operand [M][K], right [K][N], right in another order
+std::string weight_touch_macros(int64_t lines, int slot, TouchOrder order, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t GK, int eb, int threads);
 struct DmaForm { int BM, BN, WM, WN, NBUF; double t0, a0, a1, b; };
 const std::vector<DmaForm>& dma_forms();
 double dma_time(const DmaForm& f, double workgroups, int64_t nk);

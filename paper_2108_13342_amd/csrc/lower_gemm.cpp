@@ -209,11 +209,16 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // every workgroup's loop would wait for a memory round trip of its own.  Instead the workgroups of each XCD touch
   // what their tiles will read of the matrix between them (one 4-byte load per 128-byte line, landing in a spare piece
   // of LDS that nobody reads), so all of it is on its way into that XCD's L2 while the first tiles are being loaded.
-  // The tiles of an XCD are consecutive: inside one group of tile-rows they cover a run of columns, otherwise all.  Where
-  // the operand's rows of K do not lie one behind the other (a weight stored [K][N]), a run of columns is no run of lines
-  // and all of them are touched (W_PF_WHOLE).
+  // The tiles of an XCD are consecutive: inside one group of tile-rows they cover a run of columns, otherwise all.  Of a
+  // weight stored [K][N] a run of columns is a strip of every row (W_PF_STRIP lines of it); of one in another order the
+  // lines are not told apart (W_PF_WHOLE).
   // In the direct-to-LDS loop every wavefront issues W_PF_N loads (lanes past its share touch the last line again): they are
-  // counted there.
+  // counted there.  The register-staged loop touches before it loads anything, through the compiler's builtin, which then
+  // knows of no load in flight at the loop's entry: behind the first tiles, as assembly, the waits it placed for their
+  // registers moved into the loop, in front of every tile's multiplications (bf16 4174x1763x216, A read element by element:
+  // 47 us, 61).
+  // Lines of a [K][N] weight, us in a row of products (all, a run of lines as of [N][K], the strip): bf16 512x1001x3072 36.1,
+  // 42.1, 29.7; 33x4100x1000 68.5, 67.1, 53.4; f32 10x1038x1401 41.4, 41.4, 24.6; 33x2985x178 78.7, 98.3, 67.3.
   auto touch_weights = [&]() {
     const idx_t nb = tiles_m * tiles_n, x = blockIdx.x % 8, nx = nb / 8 + (x < nb % 8 ? 1 : 0);
     const idx_t t0 = bid - blockIdx.x / 8, t1 = t0 + nx - 1;
@@ -221,7 +226,6 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #if defined(W_PF_WHOLE)
     const idx_t lo = 0;
     const bool to_end = true;
-    const idx_t hi = GN;
 #elif defined(W_PF_ROWS)
     // (a filter matrix is the left operand: the tile-rows of the group, or, inside one column, those from tile to tile)
     const bool column = one && (t0 % grp) / gsz == (t1 % grp) / gsz;
@@ -231,23 +235,43 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
     const idx_t lo = one ? (t0 % grp) / gsz * BN : 0, hi = one ? ((t1 % grp) / gsz + 1) * BN : GN;
     const bool to_end = hi >= GN;
 #endif
+#if defined(W_PF_STRIP)
+    const idx_t l0 = 0, l1 = GK * W_PF_STRIP;
+#elif defined(W_PF_WHOLE)
+    const idx_t l0 = 0, l1 = W_PREFETCH_LINES;
+#else
     const idx_t l0 = (idx_t)((long long)lo * GK * ELEM_BYTES / 128), l1 = to_end ? (idx_t)W_PREFETCH_LINES : (idx_t)((long long)hi * GK * ELEM_BYTES / 128);
+#endif
     const idx_t per = (l1 - l0 + nx - 1) / nx, first = l0 + (blockIdx.x / 8) * per, end = first + per < l1 ? first + per : l1;
-    const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
 #ifdef DMA
+    const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
 #pragma unroll
     for (int i = 0; i < W_PF_N; ++i) {
       const idx_t line = first + tid + i * NT;
       load_to_lds4((const char*)W_PREFETCH_PTR + (long long)(line < end ? line : l1 - 1) * 128, spare);
     }
 #else
-    for (idx_t line = first + tid; line < end; line += NT) load_to_lds4((const char*)W_PREFETCH_PTR + (long long)line * 128, spare);
+    typedef __attribute__((address_space(1))) const void* gptr_t;
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    for (idx_t i = first + tid; i < end; i += NT) {
+#ifdef W_PF_STRIP
+      const long long row = (long long)(i / W_PF_STRIP) * GN, line = (row + lo) * ELEM_BYTES / 128 + i % W_PF_STRIP;
+      if (line * 128 >= (row + (to_end ? (idx_t)GN : hi)) * ELEM_BYTES || line >= W_PREFETCH_LINES) continue;
+#else
+      const long long line = i;
+#endif
+      __builtin_amdgcn_global_load_lds((gptr_t)((const char*)W_PREFETCH_PTR + line * 128), (lptr_t)(smem + SMEM_MAIN + (RA ? 4 * BM : 0)), 4, 0, 0);
+    }
 #endif
   };
 #else
 #define W_PF_N 0
   auto touch_weights = [&]() {};
 #endif
+#ifndef DMA
+  touch_weights();
+#endif
+
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -787,7 +811,6 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // tiles are loaded ahead, so the latency of a tile's global loads overlaps PF - 1 tiles of MFMA work.
 #pragma unroll
   for (int s = 0; s < PF; ++s) gload(s, (idx_t)s * BK);
-  touch_weights();
   lstore(0, 0, 0);
   __syncthreads();
   for (int kt0 = 0; kt0 < nk; kt0 += PF) {
@@ -1011,29 +1034,31 @@ double dma_time(const DmaForm& f, double workgroups, int64_t nk) {
 }
 
 // The macros that make a kernel touch its weight operand up front (see touch_weights in the kernel): `lines` 128-byte lines
-// of parameter `slot`, `rows`: the left operand, `whole`: its rows of K are not one behind the other.  W_PF_N, the number of
-// touches a lane of the direct-to-LDS loop issues, covers the largest share of any XCD, up to what the wait counts hold.
-std::string weight_touch_macros(int64_t lines, int slot, bool rows, bool whole, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t row_bytes, int threads) {
-  const int64_t nb = tiles_m * tiles_n, grp = 8 * tiles_n;
-  int64_t most = 1;
+// of parameter `slot`; `order` says which operand it is and how it is stored.  W_PF_N, the number of touches a lane of the
+// direct-to-LDS loop issues, covers the largest share of any XCD, up to what the wait counts hold.
+std::string weight_touch_macros(int64_t lines, int slot, TouchOrder order, int64_t tiles_m, int64_t tiles_n, int BM, int BN, int64_t GM, int64_t GN, int64_t GK, int eb, int threads) {
+  const int64_t nb = tiles_m * tiles_n, grp = 8 * tiles_n, row_bytes = GK * eb, end = order == TOUCH_ROWS ? GM : GN;
+  int64_t most = 1, widest = 1;
   for (int64_t x = 0, t0 = 0; x < 8; x++) {
     const int64_t nx = nb / 8 + (x < nb % 8 ? 1 : 0);
     if (!nx) continue;
     const int64_t t1 = t0 + nx - 1, g0 = t0 / grp * 8, gsz = std::min<int64_t>(8, tiles_m - g0);
-    int64_t lo = 0, hi = rows ? GM : GN;
-    if (t0 / grp == t1 / grp && !whole) {
+    int64_t lo = 0, hi = end;
+    if (t0 / grp == t1 / grp && order != TOUCH_WHOLE) {
       const int64_t c0 = (t0 % grp) / gsz, c1 = (t1 % grp) / gsz;
-      if (!rows) { lo = c0 * BN; hi = (c1 + 1) * BN; }
+      if (order != TOUCH_ROWS) { lo = c0 * BN; hi = (c1 + 1) * BN; }
       else { lo = (g0 + (c0 == c1 ? (t0 % grp) % gsz : 0)) * BM; hi = (g0 + (c0 == c1 ? (t1 % grp) % gsz + 1 : gsz)) * BM; }
     }
-    const int64_t n = (hi >= (rows ? GM : GN) ? lines : hi * row_bytes / 128) - lo * row_bytes / 128;
+    widest = std::max(widest, std::min(hi, end) - lo);
+    const int64_t n = (hi >= end ? lines : hi * row_bytes / 128) - lo * row_bytes / 128;
     most = std::max(most, (n + nx * threads - 1) / (nx * threads));
     t0 += nx;
   }
   std::ostringstream k;
   k << "#define W_PREFETCH_LINES " << lines << "\n#define W_PREFETCH_PTR p" << slot << "\n#define W_PF_N " << std::min<int64_t>(most, 24) << "\n";
-  if (whole) k << "#define W_PF_WHOLE 1\n";
-  else if (rows) k << "#define W_PF_ROWS 1\n";
+  if (order == TOUCH_ROWS) k << "#define W_PF_ROWS 1\n";
+  if (order == TOUCH_STRIP) k << "#define W_PF_STRIP " << (widest * eb + 127) / 128 + 1 << "\n";      // (a strip starts anywhere in a line)
+  if (order == TOUCH_WHOLE) k << "#define W_PF_WHOLE 1\n";
   return k.str();
 }
 
@@ -1615,11 +1640,14 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     const int64_t wbytes = TBt.n() * dtype_bytes(TBt.dtype);
     if (!norm && GZ == 1 && (TBt.kind == DNNF_WEIGHT || TBt.weight_only) && wbytes >= (256 << 10) && wbytes <= ((int64_t)16 << 20) &&
         wbytes == GN * K * eb && !getenv("DNNF_NO_WEIGHT_PREFETCH")) {    // (developer switch for A/B runs)
-      int64_t next = 1;                  // [N][K]: K innermost, then the columns in their own order
-      bool by_rows = true;
-      for (auto* atoms : {&katoms, &cols})
-        for (auto it = atoms->rbegin(); it != atoms->rend(); ++it) { by_rows = by_rows && stride_of(ab, *it) == next; next *= c.atom_extent[*it]; }
-      k << weight_touch_macros(wbytes / 128, 1, false, !by_rows, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K * eb, 64 * WAVES_M * WAVES_N * WAVES_K);
+      auto dense = [&](const std::vector<int>& inner, const std::vector<int>& outer) {      // one index innermost, the other around it
+        int64_t next = 1;
+        for (auto* atoms : {&inner, &outer})
+          for (auto it = atoms->rbegin(); it != atoms->rend(); ++it) { if (stride_of(ab, *it) != next) return false; next *= c.atom_extent[*it]; }
+        return true;
+      };
+      const TouchOrder order = dense(katoms, cols) ? TOUCH_COLS : !DMA && dense(cols, katoms) ? TOUCH_STRIP : TOUCH_WHOLE;
+      k << weight_touch_macros(wbytes / 128, 1, order, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K, eb, 64 * WAVES_M * WAVES_N * WAVES_K);
     }
   }
   if (TA.dtype == DNNF_F16) k << "typedef f16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_f16\n";

@@ -33,13 +33,15 @@ def test_squeeze_excite_weights_up_front(args, kw, early):
     assert len(src) == 1 and f"#define SE_ALONE {early}\n" in src[0]
 
 
-@pytest.mark.parametrize("M,K,N,dtype,rewrite,whole", [
-    (64, 1024, 1024, "bf16", True, False),                              # stored [N][K] after rewriting
-    (64, 132, 1024, "bf16", True, True),                                # K no multiple of a vector: stays [K][N]
-    (64, 1024, 1024, "bf16", False, True),                              # not rewritten
-    (64, 1001, 1024, "f32", True, True),
+@pytest.mark.parametrize("M,K,N,dtype,rewrite,strip", [
+    (64, 1024, 1024, "bf16", True, 0),                                  # stored [N][K] after rewriting
+    (64, 132, 1024, "bf16", True, 3),                                   # K no multiple of a vector: stays [K][N]; an XCD's two tiles of 64
+    (64, 1024, 1024, "bf16", False, 3),                                 # not rewritten; four tiles of 32
+    (64, 1001, 1024, "f32", True, 5),
+    (2000, 1001, 300, "f32", True, 11),                                 # an XCD's tiles cover all columns
 ])
-def test_weight_touches_cover_what_the_tiles_read(M, K, N, dtype, rewrite, whole):
+def test_weight_touches_cover_what_the_tiles_read(M, K, N, dtype, rewrite, strip):
     """A run of columns is a run of memory lines only where the weight's rows of K lie one behind the other."""
     src = _sources(U.gemm_block(M, K, N, dtype), rewrite)[0][1]
-    assert "#define W_PREFETCH_LINES" in src and ("#define W_PF_WHOLE 1" in src) == whole
+    assert "#define W_PREFETCH_LINES" in src and "#define W_PF_WHOLE" not in src
+    assert (f"#define W_PF_STRIP {strip}\n" in src) if strip else ("#define W_PF_STRIP" not in src)

@@ -8,6 +8,7 @@
 //   depthwise (group = channels): direct stencil, one output element per lane, fp32 accumulate.
 // The block's successors (folded-BN affine, activation, residual add, ...) run as the epilogue.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "lower_ctx.hpp"
@@ -256,11 +257,23 @@ Lowered lower_conv(LowerCtx& c) {
             if (HO % th == 0) { ldsTH = th; break; }
       }
     }
-    // ... but where its workgroups leave half the chip idle, more and smaller ones that read the map directly are done first: a
-    // staged one spends 4 to 7 us whatever their number (5x5, f16: 480x14x14, 15 workgroups, 6.8 us, direct 3.5; 144x56x56 at
-    // stride 2, 40 workgroups, 5.7, 3.6; 1152x7x7 4.6, 3.4).
-    const bool few = VC && ldsTH > 0 && N * ((C / VC + ldsXC - 1) / ldsXC) * (HO / ldsTH) * (WO / ldsTW) < 128;
-    bool use_lds = ldsTH > 0 && (c.opts.force_variant >= 101 || (c.opts.force_variant < 100 && KH * KW > 9 && !few));
+    // ... but a staged workgroup spends 4 to 11 us however few there are.  While they leave half the chip idle and the direct kernel
+    // has no more than two workgroups for a compute unit, that one is often done first.  Both times (us) are estimated from what they are made of: staged, the
+    // passes over the taps, the vectors a thread loads and the workgroups; direct, the workgroups on a compute unit, their taps
+    // and the filter that they read.  Fitted to 183 maps, 5x5 and 7x7, 7x7 to 112x112 pixels (3 to 9 % rms).  Direct and staged:
+    // f16 480x14x14 1 image 4.5, 7.1, 4 images 6.1, 7.1, 8 images 9.6, 7.2; 64x56x56 4 images 5.6, 8.3; 144x56x56 at stride 2 4.2,
+    // 5.7; 672x14x14 at stride 2 4.5, 3.7; f32 240x14x14 8 images 7.0, 5.6.
+    bool direct_first = false;
+    if (VC && ldsTH > 0) {
+      const bool two = VC == 8;
+      const double taps = KH * KW / 25.0, staged_wgs = (double)(N * ((C / VC + ldsXC - 1) / ldsXC) * (HO / ldsTH) * (WO / ldsTW));
+      const double w = (double)N * (C / VC) * HO * WO / 65536;
+      const double passes = std::ceil(ldsTH * ldsTW * ldsXC / 256.0), loads = std::ceil(((ldsTH - 1) * SH + KH) * ((ldsTW - 1) * SW + KW) * ldsXC / 256.0);
+      const double staged = two ? 2.0 + 1.06 * passes * taps + 0.13 * loads + 0.55 * staged_wgs / 256 : 2.3 + 0.69 * passes * taps + 0.06 * loads + 0.44 * staged_wgs / 256;
+      const double direct = two ? 2.4 + 0.76 * w * taps + 1.36 * std::ceil(w) + 0.68 * w * C / 256 + 0.3 * C / 1000 : 1.9 + 0.91 * w * taps + 1.25 * std::ceil(w) + 0.4 * w * C / 256 + 0.39 * C / 1000;
+      direct_first = staged_wgs < 128 && w <= 2 && direct < staged;
+    }
+    bool use_lds = ldsTH > 0 && (c.opts.force_variant >= 101 || (c.opts.force_variant < 100 && KH * KW > 9 && !direct_first));
     if (pool_dst >= 0) {
       // one workgroup must see every pixel of an image for its channels: the staged kernel with the whole plane as its patch
       DNNF_CHECK(VC && ldsTH == HO && ldsTW == WO && c.opts.force_variant != 100, DNNF_UNSUPPORTED_OP,

@@ -45,3 +45,21 @@ def test_weight_touches_cover_what_the_tiles_read(M, K, N, dtype, rewrite, strip
     src = _sources(U.gemm_block(M, K, N, dtype), rewrite)[0][1]
     assert "#define W_PREFETCH_LINES" in src and "#define W_PF_WHOLE" not in src
     assert (f"#define W_PF_STRIP {strip}\n" in src) if strip else ("#define W_PF_STRIP" not in src)
+
+
+@pytest.mark.parametrize("args,dtype,kernel", [
+    ((1, 480, 14, 5, 1), "f16", "dw_chan"), ((4, 480, 14, 5, 1), "f16", "dw_chan"),
+    ((8, 480, 14, 5, 1), "f16", "dw_lds"), ((5, 672, 14, 5, 1), "f16", "dw_lds"),        # under 128 staged workgroups, and they are done first
+    ((8, 240, 14, 5, 1), "f32", "dw_lds"), ((1, 240, 14, 5, 1), "f32", "dw_chan"),
+    ((2, 672, 14, 5, 2), "f16", "dw_lds"), ((1, 144, 56, 5, 2), "f16", "dw_chan"),       # small patches; large ones
+    ((6, 128, 28, 7, 1), "f16", "dw_chan"), ((16, 128, 28, 7, 1), "f16", "dw_lds"),      # 7x7
+])
+def test_depthwise_kernel_by_estimate(args, dtype, kernel):
+    N, C, H, K, stride = args
+    b = GraphBuilder("dw", dtype)
+    zeros = lambda shape: np.zeros(shape, dtype=np.float32)
+    x = configs._conv(b, b.input("x", (N, 8, H, H), zeros((N, 8, H, H))), b.weight("w0", (C, 8, 1, 1), zeros((C, 8, 1, 1))), None, 1, 0)
+    x = configs._un(b, "Relu", x)
+    b.mark_output(configs._un(b, "Relu", configs._conv(b, x, b.weight("w", (C, 1, K, K), zeros((C, 1, K, K))), None, stride, K // 2, C)))
+    names = [n for n, _ in _sources(b.finish(), layout=1) if n.startswith("dw_")]
+    assert len(names) == 1 and names[0].startswith(kernel), names

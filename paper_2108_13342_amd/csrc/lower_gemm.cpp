@@ -1542,9 +1542,6 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
       else DMA = v[7] == 1 && dma_ok && BK == 64 && NBUF >= 2 && WAVES_K == 1;
     }
   }
-  // (a tile's name says the number of buffers where it was asked for - by a tuning build or the override - and not where it is
-  // the choice made here; the tiles whose wavefronts split K are named by tile and wavefronts alone)
-  const bool named_buffers = c.opts.force_variant >= 100 || getenv("DNNF_GEMM_TILE");
   int norm_value = -1;        // expression node of the value the normalisation reads
   if (norm) {
     // eight wavefronts side by side on 32 whole rows of the product
@@ -1719,7 +1716,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   Kn.source = src;
   Lw.launches.push_back(Kn);
   Lw.variant = "mfma_" + std::to_string(BM) + "x" + std::to_string(BN) + "x" + std::to_string(BK) + "_a" + std::to_string(amode) + "b" + std::to_string(bmode) +
-               (WAVES_M * WAVES_N * WAVES_K > 4 ? "_w" + std::to_string(WAVES_M * WAVES_N * WAVES_K) : std::string()) + (DMA && WAVES_K == 1 ? (NBUF > 2 && named_buffers ? "_dma" + std::to_string(NBUF) : std::string("_dma")) : std::string()) + (norm ? "_rownorm" : "");
+               (WAVES_M * WAVES_N * WAVES_K > 4 ? "_w" + std::to_string(WAVES_M * WAVES_N * WAVES_K) : std::string()) + (DMA ? "_dma" + std::to_string(NBUF) : std::string()) + (norm ? "_rownorm" : "");
   return Lw;
 }
 

@@ -92,13 +92,13 @@ def test_gemm_tile_configurations(tile, monkeypatch):
 
 
 @pytest.mark.parametrize("M,K,N,dtype,kw,tile", [
-    (33, 768, 520, "bf16", dict(residual=True, w_transposed=True), "32x32x384_a0b0_w8"),      # whole K tiles, a row in the second tile
-    (1, 3072, 77, "f16", dict(w_transposed=True), "32x32x384_a0b0_w8"),                       # one row, columns of odd number
-    (65, 520, 96, "f16", dict(gelu=True), "32x32x128_a0b0_w8"),                               # K ends inside a tile
-    (70, 384, 40, "bf16", dict(), "32x32x384"),                                               # a single K tile
-    (31, 512, 33, "bf16", dict(bias=False, w_transposed=True), "32x32x256_a0b0_w8"),          # two K tiles
-    (40, 256, 2624, "f32", dict(residual=True), "32x32x128"),                                 # f32: 16-byte fragments
-    (33, 132, 68, "f32", dict(w_transposed=True), "32x32x64_a0b0_w8"),                        # f32, ending inside a tile
+    (33, 768, 520, "bf16", dict(residual=True, w_transposed=True), "32x32x384_a0b0_w8_dma3"),      # whole K tiles, a row in the second tile
+    (1, 3072, 77, "f16", dict(w_transposed=True), "32x32x384_a0b0_w8_dma3"),                       # one row, columns of odd number
+    (65, 520, 96, "f16", dict(gelu=True), "32x32x128_a0b0_w8_dma4"),                               # K ends inside a tile
+    (70, 384, 40, "bf16", dict(), "32x32x384_a0b0_w8_dma3"),                                               # a single K tile
+    (31, 512, 33, "bf16", dict(bias=False, w_transposed=True), "32x32x256_a0b0_w8_dma3"),          # two K tiles
+    (40, 256, 2624, "f32", dict(residual=True), "32x32x128_a0b0_w8_dma3"),                                 # f32: 16-byte fragments
+    (33, 132, 68, "f32", dict(w_transposed=True), "32x32x64_a0b0_w8_dma3"),                        # f32, ending inside a tile
     (600, 768, 1000, "f32", dict(gelu=True), "32x32x128"),                                    # more than two workgroups per compute unit
     (40, 513, 60, "f16", dict(), "32x32x64_"),                                                # element loaders keep short tiles
 ])
@@ -111,21 +111,21 @@ def test_gemm_long_k_tiles(M, K, N, dtype, kw, tile):
 
 @pytest.mark.parametrize("M,K,N,dtype,kw,tile", [
     # K ends inside a long tile, for every length (the last tile is filled up with zeros on both operands)
-    (40, 1144, 72, "f16", dict(weight=True), "32x32x384_a0b0_w8"),
-    (40, 1000, 72, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),
-    (40, 520, 72, "f16", dict(weight=True), "32x32x128_a0b0_w8"),
-    (40, 252, 72, "f32", dict(weight=True), "32x32x128_a0b0_w8"),
-    (40, 132, 72, "f32", dict(weight=True), "32x32x64_a0b0_w8"),
+    (40, 1144, 72, "f16", dict(weight=True), "32x32x384_a0b0_w8_dma3"),
+    (40, 1000, 72, "bf16", dict(weight=True), "32x32x256_a0b0_w8_dma3"),
+    (40, 520, 72, "f16", dict(weight=True), "32x32x128_a0b0_w8_dma4"),
+    (40, 252, 72, "f32", dict(weight=True), "32x32x128_a0b0_w8_dma3"),
+    (40, 132, 72, "f32", dict(weight=True), "32x32x64_a0b0_w8_dma3"),
     # the lines between the forms, on either side
-    (64, 256, 80, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),
+    (64, 256, 80, "bf16", dict(weight=True), "32x32x256_a0b0_w8_dma3"),
     (64, 248, 80, "bf16", dict(weight=True), "64x64x64_a0b0"),
-    (64, 128, 80, "f32", dict(weight=True), "32x32x128_a0b0_w8"),
+    (64, 128, 80, "f32", dict(weight=True), "32x32x128_a0b0_w8_dma3"),
     (64, 124, 80, "f32", dict(weight=True), "64x64x16_a0b0"),
-    (64, 256, 6144, "bf16", dict(weight=True), "32x32x64_a0b0"),             # 96 tiles of 64x64
-    (64, 256, 6208, "bf16", dict(weight=True), "64x64x64_a0b0_dma"),         # 97
-    (256, 768, 1024, "f16", dict(weight=True), "32x32x384_a0b0_w8"),         # one 32x32 tile per compute unit
-    (257, 768, 1024, "f16", dict(weight=True), "32x32x64_a0b0"),             # more: short tiles
-    (500, 1536, 768, "bf16", dict(weight=True), "32x32x256_a0b0_w8"),        # more, and a long K
+    (64, 256, 6144, "bf16", dict(weight=True), "32x32x64_a0b0_dma4"),             # 96 tiles of 64x64
+    (64, 256, 6208, "bf16", dict(weight=True), "64x64x64_a0b0_dma4"),         # 97
+    (256, 768, 1024, "f16", dict(weight=True), "32x32x384_a0b0_w8_dma3"),         # one 32x32 tile per compute unit
+    (257, 768, 1024, "f16", dict(weight=True), "32x32x64_a0b0_dma4"),             # more: short tiles
+    (500, 1536, 768, "bf16", dict(weight=True), "32x32x256_a0b0_w8_dma2"),        # more, and a long K
     (1200, 768, 768, "f32", dict(weight=True), "32x32x128_a0b0_w8"),         # 228 tiles of 64x64
     (64, 132, 16384, "f32", dict(weight=True), "64x64x16_a0b0"),             # 256, with too many zeros
     (64, 128, 16384, "f32", dict(weight=True), "32x32x128_a0b0_w8"),         # 256
@@ -144,8 +144,8 @@ def test_gemm_long_k_tiles(M, K, N, dtype, kw, tile):
     (704, 704, 768, "bf16", dict(a_transposed=True), "64x64x64_a1b1"),       # 132 tiles of 64x64
     (1024, 300, 1024, "f32", dict(a_transposed=True, weight=True), "64x64x16_a1b0"),
     # the product stored along its rows: the epilogue reads the eight partial tiles down their columns
-    (40, 768, 72, "bf16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8"),
-    (40, 384, 33, "f16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8"),
+    (40, 768, 72, "bf16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8_dma3"),
+    (40, 384, 33, "f16", dict(weight=True, out_transposed=True), "32x32x384_a0b0_w8_dma3"),
     (72, 256, 64, "f16", dict(batch=(3,), out_transposed=True), "32x32x256_a0b1_w8"),
     (44, 256, 36, "f32", dict(a_transposed=True, out_transposed=True), "32x32x128_a1b1_w8"),
 ])
@@ -167,7 +167,7 @@ def test_gemm_tiles_loaded_straight_into_lds(tile, dtype, N, monkeypatch):
     s, _ = check_against_oracle(U.gemm_block(300, 768, N, dtype, residual=True, w_transposed=True))
     bm, bn = tile.split(",")[:2]
     names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
-    assert names[0].startswith(f"mfma_{bm}x{bn}x64") and names[0].endswith("_dma"), names
+    assert names[0].startswith(f"mfma_{bm}x{bn}x64") and names[0].endswith("_dma2"), names
 
 
 @pytest.mark.parametrize("tile,K", [("64,64,64,2,2,3,1,1", 768), ("128,64,64,4,2,4,1,1", 768), ("128,128,64,2,4,3,1,1", 768),

@@ -26,12 +26,12 @@ def _kernel(M, K, N, dtype, batch=(), a_transposed=False, weight=True):
 
 @pytest.mark.parametrize("M,K,N,kw,tile", [
     # a K that no length divides: the number of tiles counts, not the padding alone
-    (40, 3080, 768, {}, "32x32x256_a0b0_w8"),
-    (40, 3136, 768, {}, "32x32x256_a0b0_w8"),
-    (40, 520, 768, {}, "32x32x128_a0b0_w8"),
-    (40, 1000, 768, {}, "32x32x256_a0b0_w8"),
-    (300, 1288, 768, {}, "32x32x128_a0b0_w8"),
-    (33, 3072, 768, {}, "32x32x384_a0b0_w8"),
+    (40, 3080, 768, {}, "32x32x256_a0b0_w8_dma3"),
+    (40, 3136, 768, {}, "32x32x256_a0b0_w8_dma3"),
+    (40, 520, 768, {}, "32x32x128_a0b0_w8_dma4"),
+    (40, 1000, 768, {}, "32x32x256_a0b0_w8_dma3"),
+    (300, 1288, 768, {}, "32x32x128_a0b0_w8_dma4"),
+    (33, 3072, 768, {}, "32x32x384_a0b0_w8_dma3"),
     # transposing loaders: fewer, longer tiles
     (640, 640, 64, dict(batch=(6,), weight=False), "32x32x384_a0b1_w8"),
     (320, 640, 640, dict(a_transposed=True, weight=False), "32x32x384_a1b1_w8"),
@@ -43,26 +43,34 @@ def test_length_of_k_tiles_16_bit(M, K, N, kw, tile):
     assert _kernel(M, K, N, "bf16", **kw) == "mfma_" + tile
 
 
-@pytest.mark.parametrize("K,bk", [(128, 128), (132, 64), (192, 64), (256, 128), (576, 64), (1000, 128), (3080, 64)])
-def test_length_of_k_tiles_f32(K, bk):
-    assert _kernel(256, K, 768, "f32") == f"mfma_32x32x{bk}_a0b0_w8"
+@pytest.mark.parametrize("K,bk,buffers", [(128, 128, 3), (132, 64, 3), (192, 64, 3), (256, 128, 3), (576, 64, 4), (1000, 128, 3), (3080, 64, 3)])
+def test_length_of_k_tiles_f32(K, bk, buffers):
+    assert _kernel(256, K, 768, "f32") == f"mfma_32x32x{bk}_a0b0_w8_dma{buffers}"
+
+
+@pytest.mark.parametrize("M,K,N,tile", [
+    (256, 768, 1024, "32x32x64_a0b0_w8_dma4"), (257, 768, 1024, "32x32x128_a0b0_w8"),          # 256 and 288 tiles: straight into LDS, through registers
+    (256, 700, 1024, "32x32x64_a0b0_w8_dma3"), (288, 700, 1024, "32x32x64_a0b0_w8"),
+])
+def test_line_of_direct_to_lds_tiles_f32(M, K, N, tile):
+    assert _kernel(M, K, N, "f32") == "mfma_" + tile
 
 
 @pytest.mark.parametrize("M,K,N,kw,tile", [
     # more than one 32x32 tile per compute unit, both operands read along K: short tiles ...
-    (500, 768, 768, {}, "32x32x64_a0b0"),
-    (900, 512, 768, {}, "32x32x64_a0b0"),
-    (900, 768, 768, {}, "32x32x64_a0b0"),
-    (400, 384, 768, {}, "32x32x64_a0b0"),
-    (300, 768, 2304, {}, "32x32x64_a0b0"),
+    (500, 768, 768, {}, "32x32x64_a0b0_dma4"),
+    (900, 512, 768, {}, "32x32x64_a0b0_dma4"),
+    (900, 768, 768, {}, "32x32x64_a0b0_dma4"),
+    (400, 384, 768, {}, "32x32x64_a0b0_dma4"),
+    (300, 768, 2304, {}, "32x32x64_a0b0_dma4"),
     # ... unless K is long, the weight larger than an L2 cache, or the chip not full
-    (900, 1528, 768, {}, "32x32x64_a0b0"),
-    (900, 1536, 768, {}, "32x32x256_a0b0_w8"),
-    (128, 512, 4096, {}, "32x32x64_a0b0"),
-    (128, 512, 4104, {}, "32x32x256_a0b0_w8"),
-    (128, 768, 3072, {}, "32x32x256_a0b0_w8"),
-    (256, 768, 1024, {}, "32x32x384_a0b0_w8"),
-    (257, 768, 1024, {}, "32x32x64_a0b0"),
+    (900, 1528, 768, {}, "32x32x64_a0b0_dma4"),
+    (900, 1536, 768, {}, "32x32x256_a0b0_w8_dma2"),
+    (128, 512, 4096, {}, "32x32x64_a0b0_dma4"),
+    (128, 512, 4104, {}, "32x32x256_a0b0_w8_dma2"),
+    (128, 768, 3072, {}, "32x32x256_a0b0_w8_dma2"),
+    (256, 768, 1024, {}, "32x32x384_a0b0_w8_dma3"),
+    (257, 768, 1024, {}, "32x32x64_a0b0_dma4"),
     (512, 512, 64, dict(batch=(12,), weight=False), "32x32x256_a0b1_w8"),
 ])
 def test_short_k_tiles_where_workgroups_hide_each_other(M, K, N, kw, tile):
@@ -90,11 +98,11 @@ def test_line_for_a_transposed_left_operand(M, K, N, dtype, weight, tile):
 
 
 @pytest.mark.parametrize("M,K,N,dtype,tile", [
-    (384, 256, 1024, "bf16", "32x32x64_a0b0"), (385, 256, 1024, "bf16", "64x64x64_a0b0_dma"),              # K below 512: 96 tiles, 112 tiles
-    (64, 248, 768, "bf16", "64x64x64_a0b0"), (64, 256, 768, "bf16", "32x32x256_a0b0_w8"),                  # the smallest K in 16 bits
-    (704, 1536, 1024, "f16", "32x32x256_a0b0_w8"), (768, 1536, 1024, "f16", "64x64x64_a0b0_dma"),          # 176 tiles, 192 tiles
+    (384, 256, 1024, "bf16", "32x32x64_a0b0_dma4"), (385, 256, 1024, "bf16", "64x64x64_a0b0_dma4"),              # K below 512: 96 tiles, 112 tiles
+    (64, 248, 768, "bf16", "64x64x64_a0b0"), (64, 256, 768, "bf16", "32x32x256_a0b0_w8_dma3"),                  # the smallest K in 16 bits
+    (704, 1536, 1024, "f16", "32x32x256_a0b0_w8_dma2"), (768, 1536, 1024, "f16", "64x64x64_a0b0_dma4"),          # 176 tiles, 192 tiles
     (1024, 256, 1024, "f32", "32x32x128_a0b0_w8"), (1088, 256, 1024, "f32", "128x64x16_a0b0"),             # 256 tiles, 272 tiles
-    (64, 124, 768, "f32", "64x64x16_a0b0"), (64, 128, 768, "f32", "32x32x128_a0b0_w8"),                    # the smallest K in f32
+    (64, 124, 768, "f32", "64x64x16_a0b0"), (64, 128, 768, "f32", "32x32x128_a0b0_w8_dma3"),                    # the smallest K in f32
 ])
 def test_lines_between_tile_forms(M, K, N, dtype, tile):
     assert _kernel(M, K, N, dtype) == "mfma_" + tile
@@ -106,7 +114,7 @@ def test_lines_between_tile_forms(M, K, N, dtype, tile):
     (500, 136, 900, (), "32x32x16_a0b0"),
     (1024, 132, 1024, (), "64x64x16_a0b0"),
     (1024, 200, 1024, (), "64x64x16_a0b0"),
-    (256, 132, 768, (), "32x32x64_a0b0_w8"),              # the chip is not full
+    (256, 132, 768, (), "32x32x64_a0b0_w8_dma3"),              # the chip is not full
     (700, 160, 768, (), "32x32x64_a0b0_w8"),              # few zeros
     (1024, 256, 1024, (), "32x32x128_a0b0_w8"),
     (200, 200, 64, (40,), "32x32x128_a0b1_w8"),           # the transposing loader gains all the same

@@ -1481,15 +1481,14 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
   if (zeros) split_k = n64 < 192 && K >= 128;
   if (c.opts.force_variant < 100 && split_k) {
     f = {32, 32, BK0, 1, 1, 4, 1, 2};
-    // 16 bits, direct loads, more than one workgroup per compute unit: the workgroups hide each other's round trips, and
-    // short tiles leave room for more of them.  Short against long tiles, us in a loop and (in brackets) in a row of
-    // products whose weights come from beyond the L2 caches: 500x768x768 4.6 (5.9), 4.9 (6.1); 600x768x768 4.7 (5.9), 4.9
-    // (6.0); 900x512x768 4.6 (5.6), 5.1 (5.8); 900x768x768 5.6 (6.9), 6.1 (7.0); 400x384x768 3.6 (4.2), 3.8 (4.5).  Long
-    // tiles where K is long (500x1536x768: 6.8 (9.0), 6.9 (8.9); 600x1536x768: 6.9 (10.2), 6.9 (9.0); 900x3072x768:
-    // 18.2 (19.9), 17.6 (19.1)) or the right operand larger than an L2 cache of 4 MB (128x768x3072: 8.5 (9.9), 8.1 (9.6);
-    // 96x1024x4096: 14.1 (15.2), 13.2 (14.2)); between 2 and 4 MB it is one way in a loop and the other in a row
-    // (300x768x2304: 6.3 (9.1), 6.7 (8.8)).
-    const bool long_16 = !direct || n32 <= 256 || K >= 1536 || (K >= 512 && n32 > 320 && GZ * GN * K * eb > (4 << 20));
+    // 16 bits, direct loads, more than one workgroup per compute unit: the workgroups hide each other's round trips, and short
+    // tiles leave room for more of them.  Short against the better of the long tiles on the direct-to-LDS loop, us in a row of
+    // products whose weights come from beyond the L2 caches, M x K x N (32x32 tiles): 72x768x3072 (288) 4.4, 4.9; 257x1024x1056
+    // (297) 5.9, 6.0; 320x768x1024 (320) 5.2, 5.4; 352x768x1024 (352) 5.2, 5.3; 96x1024x4096 (384) 5.4, 5.7; 64x640x6400 (400)
+    // 4.6, 4.9; 128x1024x4096 (512) 5.4, 5.7; 500x1536x768 (384) 5.9, 6.2; 128x2048x2304 (288) 7.7, 7.7; 900x3072x768 (696)
+    // 17.7, 17.1; 64x4096x5000 (314) 12.5, 13.0.  Of 95 products of 258 to 696 tiles, K 512 to 4096, weights of 1 to 39 MB, the
+    // long tiles win six by more than 2 % (600x2560x768 by 6 %, 96x2560x4096 by 5 %).
+    const bool long_16 = !direct || n32 <= 256;
     // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
     // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile
     // costs what `share` values of K would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5,
@@ -1525,7 +1524,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // 200x1536x384 5.2, 4.5; 500x768x768 4.8, 4.3; 257x768x1024 5.5, 4.7; 900x768x768 6.8, 6.4; 300x768x2304 8.2, 7.5.
     if (vec_loads && eb == 2 && direct && !getenv("DNNF_GEMM_NO_DMA")) {
       f.DMA = 1;
-      f.NBUF = f.WK == 4 ? 4 : f.BK == 384 ? 3 : f.BK == 256 ? (n32 <= 256 ? 3 : 2) : (n32 <= 256 ? 4 : 3);
+      f.NBUF = f.BK >= 256 ? 3 : 4;
     }
   }
   int BM = f.BM, BN = f.BN, BK = f.BK, WAVES_M = f.WM, WAVES_N = f.WN, WAVES_K = f.WK, NBUF = f.NBUF, PF = f.PF, DMA = f.DMA;

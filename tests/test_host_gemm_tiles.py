@@ -63,12 +63,15 @@ def test_line_of_direct_to_lds_tiles_f32(M, K, N, tile):
     (900, 768, 768, {}, "32x32x64_a0b0_dma4"),
     (400, 384, 768, {}, "32x32x64_a0b0_dma4"),
     (300, 768, 2304, {}, "32x32x64_a0b0_dma4"),
-    # ... unless K is long, the weight larger than an L2 cache, or the chip not full
+    # ... whatever the length of K and the size of the weight (more than 4 MB from the third on)
     (900, 1528, 768, {}, "32x32x64_a0b0_dma4"),
-    (900, 1536, 768, {}, "32x32x256_a0b0_w8_dma2"),
+    (900, 1536, 768, {}, "32x32x64_a0b0_dma4"),
+    (72, 768, 3072, {}, "32x32x64_a0b0_dma4"),            # 288 tiles
+    (96, 1024, 4096, {}, "32x32x64_a0b0_dma4"),           # 384
     (128, 512, 4096, {}, "32x32x64_a0b0_dma4"),
-    (128, 512, 4104, {}, "32x32x256_a0b0_w8_dma2"),
-    (128, 768, 3072, {}, "32x32x256_a0b0_w8_dma2"),
+    (128, 512, 4104, {}, "32x32x64_a0b0_dma4"),
+    (128, 768, 3072, {}, "32x32x64_a0b0_dma4"),
+    # ... unless the chip is not full
     (256, 768, 1024, {}, "32x32x384_a0b0_w8_dma3"),
     (257, 768, 1024, {}, "32x32x64_a0b0_dma4"),
     (512, 512, 64, dict(batch=(12,), weight=False), "32x32x256_a0b1_w8"),
@@ -100,7 +103,7 @@ def test_line_for_a_transposed_left_operand(M, K, N, dtype, weight, tile):
 @pytest.mark.parametrize("M,K,N,dtype,tile", [
     (384, 256, 1024, "bf16", "32x32x64_a0b0_dma4"), (385, 256, 1024, "bf16", "64x64x64_a0b0_dma4"),              # K below 512: 96 tiles, 112 tiles
     (64, 248, 768, "bf16", "64x64x64_a0b0"), (64, 256, 768, "bf16", "32x32x256_a0b0_w8_dma3"),                  # the smallest K in 16 bits
-    (704, 1536, 1024, "f16", "32x32x256_a0b0_w8_dma2"), (768, 1536, 1024, "f16", "64x64x64_a0b0_dma4"),          # 176 tiles, 192 tiles
+    (704, 1536, 1024, "f16", "32x32x64_a0b0_dma4"), (768, 1536, 1024, "f16", "64x64x64_a0b0_dma4"),          # 176 tiles, 192 tiles
     (1024, 256, 1024, "f32", "32x32x128_a0b0_w8"), (1088, 256, 1024, "f32", "128x64x16_a0b0"),             # 256 tiles, 272 tiles
     (64, 124, 768, "f32", "64x64x16_a0b0"), (64, 128, 768, "f32", "32x32x128_a0b0_w8_dma3"),                    # the smallest K in f32
 ])

@@ -1486,9 +1486,11 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // products whose weights come from beyond the L2 caches, M x K x N (32x32 tiles): 72x768x3072 (288) 4.4, 4.9; 257x1024x1056
     // (297) 5.9, 6.0; 320x768x1024 (320) 5.2, 5.4; 352x768x1024 (352) 5.2, 5.3; 96x1024x4096 (384) 5.4, 5.7; 64x640x6400 (400)
     // 4.6, 4.9; 128x1024x4096 (512) 5.4, 5.7; 500x1536x768 (384) 5.9, 6.2; 128x2048x2304 (288) 7.7, 7.7; 900x3072x768 (696)
-    // 17.7, 17.1; 64x4096x5000 (314) 12.5, 13.0.  Of 95 products of 258 to 696 tiles, K 512 to 4096, weights of 1 to 39 MB, the
-    // long tiles win six by more than 2 % (600x2560x768 by 6 %, 96x2560x4096 by 5 %).
-    const bool long_16 = !direct || n32 <= 256;
+    // 17.7, 17.1; 64x4096x5000 (314) 12.5, 13.0.  Where K is no whole number of short tiles a row starts anywhere in a 128-byte
+    // line, and 128 bytes of it lie in two: long tiles read fewer lines twice, and pay from some length on: 500x3072x768 9.6,
+    // 9.6 but 500x3080x768 12.5, 11.1; 410x1928x833 12.6, 10.5; 64x1400x8000 8.2, 7.4; 96x1480x2900 7.9, 7.2; 100x1000x4000 6.2,
+    // 6.0; 72x776x3072 5.2, 5.1; 64x520x6400 4.7, 4.9.
+    const bool long_16 = !direct || n32 <= 256 || (K % 64 != 0 && (K >= 1536 || (K >= 1024 && GZ * GN * K * eb > (4 << 20))));
     // Length of the long K tile.  f32: 128, or 64 where that pads K by a tile less (128x704x768: 9.3 and 8.8 us with 128 and
     // 64, 128x2048x768: 20.9 and 21.2, 256x256x768: 5.0 and 4.8).  16 bits: the length of the least work, where a tile
     // costs what `share` values of K would (us with 128, 256 and 384).  Little between direct loads: 40x896x768 6.4, 6.5,
@@ -1524,7 +1526,7 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
     // 200x1536x384 5.2, 4.5; 500x768x768 4.8, 4.3; 257x768x1024 5.5, 4.7; 900x768x768 6.8, 6.4; 300x768x2304 8.2, 7.5.
     if (vec_loads && eb == 2 && direct && !getenv("DNNF_GEMM_NO_DMA")) {
       f.DMA = 1;
-      f.NBUF = f.BK >= 256 ? 3 : 4;
+      f.NBUF = f.WK == 4 ? 4 : f.BK == 384 ? 3 : f.BK == 256 ? (n32 <= 256 ? 3 : 2) : (n32 <= 256 ? 4 : 3);
     }
   }
   int BM = f.BM, BN = f.BN, BK = f.BK, WAVES_M = f.WM, WAVES_N = f.WN, WAVES_K = f.WK, NBUF = f.NBUF, PF = f.PF, DMA = f.DMA;

@@ -63,15 +63,20 @@ def test_line_of_direct_to_lds_tiles_f32(M, K, N, tile):
     (900, 768, 768, {}, "32x32x64_a0b0_dma4"),
     (400, 384, 768, {}, "32x32x64_a0b0_dma4"),
     (300, 768, 2304, {}, "32x32x64_a0b0_dma4"),
-    # ... whatever the length of K and the size of the weight (more than 4 MB from the third on)
-    (900, 1528, 768, {}, "32x32x64_a0b0_dma4"),
+    # ... whatever the length of K and the size of the weight (more than 4 MB from the second on)
     (900, 1536, 768, {}, "32x32x64_a0b0_dma4"),
     (72, 768, 3072, {}, "32x32x64_a0b0_dma4"),            # 288 tiles
     (96, 1024, 4096, {}, "32x32x64_a0b0_dma4"),           # 384
     (128, 512, 4096, {}, "32x32x64_a0b0_dma4"),
     (128, 512, 4104, {}, "32x32x64_a0b0_dma4"),
     (128, 768, 3072, {}, "32x32x64_a0b0_dma4"),
-    # ... unless the chip is not full
+    # ... unless rows of K start anywhere in a memory line, and K is long or both it and the weight are
+    (900, 1528, 768, {}, "32x32x64_a0b0_dma4"),
+    (900, 1544, 768, {}, "32x32x128_a0b0_w8_dma3"),
+    (200, 1400, 1400, {}, "32x32x64_a0b0_dma4"),
+    (64, 1400, 8000, {}, "32x32x128_a0b0_w8_dma3"),
+    (72, 776, 3072, {}, "32x32x64_a0b0_dma4"),
+    # ... or the chip is not full
     (256, 768, 1024, {}, "32x32x384_a0b0_w8_dma3"),
     (257, 768, 1024, {}, "32x32x64_a0b0_dma4"),
     (512, 512, 64, dict(batch=(12,), weight=False), "32x32x256_a0b1_w8"),

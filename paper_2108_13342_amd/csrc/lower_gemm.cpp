@@ -348,13 +348,13 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // this wavefront's fragment reads by LDS_WAIT.
 #define TILE_BARRIER() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); asm volatile("" ::: "memory"); }
   // NBUF buffers: tile kt lives in buffer kt % NBUF and the loads run DMA_D = NBUF - 1 tiles ahead of the multiplications
-  // (one where K does not hold the 2 DMA_D - 1 tiles that the schedule is written for).  A wavefront's loads complete in
+  // (fewer where K does not hold the 2 DMA_D - 1 tiles that the schedule is written for).  A wavefront's loads complete in
   // order, so "tile kt has landed" is a wait until at most the loads issued behind it are outstanding.
   // What the pipeline is worth, 64x64 tiles with two buffers whose loads were waited for at once, with two and with three
   // buffers, us with bias: bf16 1024x3072x768 36.9, 26.6, 15.9; 4096x3072x768 39.6, 34.3, 35.6 (128x128 on three buffers
   // 49.0, 28.4); 1024x768x768 8.9, 6.4, 5.9; 256x768x2304 7.2, 6.4, 5.8.
 #define DMA_NK ((GK + BK - 1) / BK)
-#define DMA_D (DMA_NK >= 2 * NBUF - 3 ? NBUF - 1 : 1)
+#define DMA_D (DMA_NK >= 2 * NBUF - 3 ? NBUF - 1 : (DMA_NK + 1) / 2)
 #define DMA_LPT (A_DIRECT_N + B_DIRECT_N)                 // load instructions per wavefront and tile
   // Tiles 0 .. DMA_D - 1 are issued first, the touches of the weight operand behind them, the other tiles one by one in
   // the loop; a tile of the first group has landed when what was issued behind it may still be outstanding.
@@ -363,6 +363,7 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   touch_weights();
   constexpr int_c<0> no{};
   constexpr int_c<1> yes{};
+  static_assert((DMA_D - 1) * DMA_LPT + W_PF_N < 64, "more loads in flight than a wait can count");
   constexpr int_c<(DMA_D - 1) * DMA_LPT + W_PF_N> behind_touches{};
   constexpr int_c<(DMA_D - 1) * DMA_LPT> steady{};
   int buf = 0;

@@ -171,11 +171,26 @@ def test_gemm_tiles_loaded_straight_into_lds(tile, dtype, N, monkeypatch):
 
 
 @pytest.mark.parametrize("tile,K", [("64,64,64,2,2,3,1,1", 768), ("128,64,64,4,2,4,1,1", 768), ("128,128,64,2,4,3,1,1", 768),
-                                    ("64,64,64,2,2,4,1,1", 128), ("64,64,64,2,2,3,1,1", 64), ("128,128,64,4,4,4,1,1", 192)])
+                                    ("64,64,64,2,2,4,1,1", 128), ("64,64,64,2,2,3,1,1", 64), ("128,128,64,4,4,4,1,1", 192),
+                                    ("64,64,64,2,2,3,1,1", 192), ("64,64,64,2,2,4,1,1", 320),        # the fewest tiles of the full depth
+                                    ("64,128,64,2,4,4,1,1", 192), ("64,64,64,2,2,4,1,1", 256)])      # two ahead on four buffers
 def test_gemm_direct_to_lds_on_three_and_four_buffers(tile, K, monkeypatch):
     """The direct-to-LDS loop with loads two and three tiles ahead, also on products with fewer K tiles than buffers."""
     monkeypatch.setenv("DNNF_GEMM_TILE", tile)
     s, _ = check_against_oracle(U.gemm_block(300, K, 520, "bf16", residual=True, w_transposed=True))
+    names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
+    assert names[0].endswith("_dma" + tile.split(",")[5]), names
+
+
+@pytest.mark.parametrize("tile,dtype,K", [
+    ("32,32,64,1,1,4,2,1", "f32", 192), ("32,32,64,1,1,4,2,1", "f32", 320), ("32,32,64,1,1,3,2,1", "f32", 180),
+    ("32,32,128,1,1,4,2,1", "bf16", 512), ("32,32,128,1,1,3,2,1", "f16", 360), ("32,32,64,1,1,4,1,1", "bf16", 200),
+    ("32,32,384,1,1,2,2,1", "f16", 384), ("32,32,64,1,1,4,1,1", "f16", 64),
+])
+def test_gemm_direct_to_lds_split_k_by_number_of_tiles(tile, dtype, K, monkeypatch):
+    """One to six K tiles on two to four buffers, wavefronts splitting K, a weight that is touched up front."""
+    monkeypatch.setenv("DNNF_GEMM_TILE", tile)
+    s, _ = check_against_oracle(U.gemm_block(45, K, 2056, dtype, w_transposed=True))
     names = [d["kernel_name"].split(":")[1] for d in s.plan.describe() if d["family"] == 2 and not d["prepare_only"]]
     assert names[0].endswith("_dma" + tile.split(",")[5]), names
 
@@ -379,6 +394,8 @@ def test_conv_block(args, kw):
     ((2, 16, 107, 106, 24, 3), dict(dtype="bf16"), "32x128x64_dma2"),            # K of 144; few output channels
     ((1, 24, 130, 131, 72, 3), dict(), "_dma"),                                  # tiles without K split, ragged both ways
     ((1, 136, 20, 19, 72, 1), dict(), "32x32x64_dma4"),                          # pointwise
+    ((2, 72, 31, 29, 64, 3), dict(), "_dma"),                                    # a filter of 81 KB, touched up front
+    ((1, 200, 23, 21, 168, 1), dict(dtype="bf16"), "_dma"),                      # 66 KB, row by row in the last lines
 ])
 def test_conv_direct_to_lds(args, kw, variant):
     """16-bit convolutions on channels-last maps load straight into LDS: K that ends inside a tile, maps that end inside a
@@ -413,6 +430,28 @@ def test_conv_few_outputs_with_operators_in_front(front, args, kw, dtype):
 def test_pointwise_operand_stored_in_another_type(args, dtype):
     s, _ = check_against_oracle(U.front_conv_block("Cast", *args, dtype=dtype), rewrite=dtype != "f32")
     assert _families(s) == [3], s.plan.describe()
+
+
+@pytest.mark.parametrize("args,kw", [
+    ((1, 60, 20, 20, 40, 3), dict(dtype="f16")),                                 # K of 540: its last tile is not full, and wavefronts split it
+    ((1, 60, 20, 20, 40, 3), dict(dtype="bf16", act="relu")),
+    ((1, 75, 26, 27, 40, 3), dict(dtype="f32")),
+    ((2, 30, 18, 22, 33, 5), dict(dtype="f16")),
+    ((2, 90, 37, 41, 33, 3), dict(dtype="bf16", stride=2)),
+])
+def test_conv_gathers_without_branches(args, kw):
+    s, _ = check_against_oracle(U.conv_block(*args, **kw))
+    src = [(d["kernel_name"], s.plan.block_source(i)) for i, d in enumerate(s.plan.describe()) if d["family"] == 3]
+    assert len(src) == 1 and src[0][0].endswith("b3") and "#define GATHER_NO_BRANCH 1" in src[0][1], src[0][0]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("scale", [2, 3])
+def test_replicated_results_leave_as_vectors(scale, dtype):
+    """A convolution's result on a channels-last map, stored at scale x scale destinations."""
+    s, _ = check_against_oracle(U.conv_upsample_block(2, 24, 11, 9, 40, scale, dtype), layout=1)
+    src = [s.plan.block_source(i) for i, d in enumerate(s.plan.describe()) if "Resize" in d["ops"] and d["family"] == 3]
+    assert len(src) == 1 and "#define EPI_T 1" in src[0] and f"#define EPI_VEC {8 if dtype == 'f16' else 4}" in src[0]
 
 
 def test_conv_variants_chosen():

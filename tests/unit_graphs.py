@@ -167,6 +167,20 @@ def front_conv_block(front, N, C, H, W, CO, dtype="f16", keep=False, seed=43):
     return b.finish()
 
 
+def conv_upsample_block(N, C, H, W, CO, scale=2, dtype="f16", seed=44):
+    """Pointwise convolution with Relu -> nearest Resize -> 3 x 3 convolution: with data formats selected, the enlarged map is
+    stored channels-last by the first convolution."""
+    st = _st(seed)
+    b = GraphBuilder("conv_upsample_block", dtype)
+    x = b.input("x", (N, C, H, W), st.normal((N, C, H, W), 0.0, 1.0, dtype))
+    w0 = b.weight("w0", (CO, C, 1, 1), st.normal((CO, C, 1, 1), 0.0, math.sqrt(2.0 / C), dtype))
+    w1 = b.weight("w1", (CO, CO, 3, 3), st.normal((CO, CO, 3, 3), 0.0, math.sqrt(2.0 / (9 * CO)), dtype))
+    y = configs._un(b, "Relu", configs._conv(b, x, w0, None, 1, 0))
+    y = b.op("Resize", [y], (N, CO, H * scale, W * scale), {"scales": [1.0, 1.0, float(scale), float(scale)]})
+    b.mark_output(configs._conv(b, y, w1, None, 1, 1))
+    return b.finish()
+
+
 def se_tail_block(N, C, H, W, CR, dtype="f16", scale=True, bias=True, act="swish", seed=38, dw=None):
     """The squeeze-excite tail of a mobile-network block: GlobalAveragePool -> 1x1 Conv (C -> CR) -> swish (or Relu) ->
     1x1 Conv (CR -> C) -> Sigmoid [-> x * s].  H = W = 1: the first layer reads an already pooled vector.

@@ -795,7 +795,7 @@ Lowered lower_conv(LowerCtx& c) {
     // operand's values on their way.  A tap in the padding reads zeros.  Register-staged and this, us: 3x3 channels-last f16
     // 32x64x56x56 -> 64 27.2, 16.2; 32x128x28x28 -> 128 22.0, 13.4; 8x256x32x32 -> 128 17.4, 13.9; 8x128x64x64 -> 64 13.5, 9.8;
     // 8x64x128x128 -> 32 18.7, 11.7; 2x128x22x22 -> 64 7.2, 4.1.
-    const bool dma_ok = eb == 2 && amode == 0 && !dot && !prologue && (bmode == 4 || bmode == 0) && K >= 128 && !getenv("DNNF_CONV_NO_DMA");      // (developer switch for A/B runs)
+    const bool dma_ok = eb == 2 && amode == 0 && !dot && !prologue && (bmode == 4 || bmode == 0) && K >= 128;
     size_t dma_pick = 0;
     if (dma_ok) {
       // Up to 704 tiles of 32x32: wavefronts split K, eight on tiles of 128 values where K is long and the chip is not full (2x128x22x22
@@ -836,13 +836,7 @@ Lowered lower_conv(LowerCtx& c) {
     BK = tiles[pick].BK;
     // a K-split kernel is a chain of dependent K steps: fewer, longer steps keep more loads in flight
     if (WAVES_K == 4 && eb == 4 && K >= 256) BK = 64;
-    int dma = tiles[pick].nbuf;
-    if (const char* e = getenv("DNNF_CONV_TILE")) {       // developer override for tuning runs: BM,BN,BK,WAVES_M,WAVES_N,WAVES_K,NBUF[,MIN_K]
-      int v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7) >= 7 && dma_ok && K >= v[7]) {
-        BM = v[0]; BN = v[1]; BK = v[2]; WAVES_M = v[3]; WAVES_N = v[4]; WAVES_K = v[5]; dma = v[6];
-      }
-    }
+    const int dma = tiles[pick].nbuf;
     if (dma) {
       const int vec = 16 / eb, nt = 64 * WAVES_M * WAVES_N * WAVES_K;
       DNNF_CHECK((BM * BK / vec) % nt == 0 && (BN * BK / vec) % nt == 0 && dma >= 2 && dma <= 4, DNNF_UNSUPPORTED_OP, "tile does not divide into whole load passes");

@@ -1540,7 +1540,8 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
         v[0] % (32 * v[3]) == 0 && v[1] % (32 * v[4]) == 0 && v[2] % (eb == 2 ? 16 : 4) == 0 && (v[5] == 1 || v[5] == 2 || (v[7] == 1 && v[5] <= 4 && v[5] >= 1))) {
       BM = v[0]; BN = v[1]; BK = v[2]; WAVES_M = v[3]; WAVES_N = v[4]; NBUF = v[5]; WAVES_K = std::max(1, 4 / (v[3] * v[4]));
       if (v[6] >= 1 && v[6] <= 4) PF = v[6];
-      if (v[7] == 1 && v[3] * v[4] == 1 && amode == 0 && bmode == 0 && NBUF >= 2) { WAVES_K = 4 * std::max(1, v[6]); DMA = 1; }      // K split: four or eight wavefronts
+      const int kwaves = v[6] == 2 ? 8 : 4;                // K split, straight into LDS: four or eight wavefronts
+      if (v[7] == 1 && BM == 32 && BN == 32 && amode == 0 && bmode == 0 && NBUF >= 2 && BK > 0 && BK % (kwaves * (eb == 2 ? 16 : 8)) == 0) { WAVES_K = kwaves; DMA = 1; }
       else DMA = v[7] == 1 && dma_ok && BK == 64 && NBUF >= 2 && WAVES_K == 1;
     }
   }

@@ -48,3 +48,11 @@ def test_pointwise_operand_stored_in_another_type(args, dtype, tmp_path):
 @pytest.mark.parametrize("seed", [139, 231, 380])
 def test_random_networks_with_operators_in_front(seed, tmp_path):
     assert api.precompile_spec(U.random_cnn(seed, "f16", n_ops=10 + seed % 7), cache_dir=str(tmp_path), layout=1) > 0
+
+
+def test_environment_does_not_reach_convolution_tiles(monkeypatch):
+    """(An override without checks once divided by the wavefront counts it was given.)"""
+    spec = U.conv_pair_block(2, 48, 43, 41, 40, 3)
+    plain = _kernels(spec, layout=1)
+    monkeypatch.setenv("DNNF_CONV_TILE", "32,32,64,0,0,0,2")
+    assert _kernels(spec, layout=1) == plain

@@ -83,6 +83,7 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
 #define KEY(j) ((SK % BJ == 0) ? (idx_t)(j) : ((j) < SK ? (idx_t)(j) : (idx_t)(SK - 1)))
 // start of a group of 4 keys (SK no multiple of 4: the score operators clamp key by key)
 #define KEY4(j) ((SK % BJ == 0) ? (idx_t)(j) : ((j) < SK ? (idx_t)(j) : (idx_t)(SK % 4 == 0 ? SK - 4 : SK - 1)))
+  // (behind the last key a value is zero and not the last key's again: an infinity times its probability of zero would be NaN)
   auto gload = [&](const idx_t j0) {
 #if K_MODE == 0
     // keys stored [key][d], d contiguous: one 16-byte vector per (key, d-octet)
@@ -110,6 +111,7 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
       const int v = (BJ * DV / 8 % 256 == 0 || tid + i * 256 < BJ * DV / 8) ? tid + i * 256 : 0;
       const int dv = v / (BJ / 8), jb = (v % (BJ / 8)) * 8;
       rv[i] = *(const u16x8*)(Vb + offV_col(dv) + offV_k(KEY(j0 + jb) / 8 * 8));
+      if (SK % BJ != 0 && j0 + jb >= SK) rv[i] = 0;
     }
 #else
     // values stored [key][dv], dv contiguous: a thread owns 8 keys x 2 channels (every thread takes part in the
@@ -119,7 +121,10 @@ extern "C" __global__ __launch_bounds__(256) void KNAME(KPARAMS) {
       const int s = (BJ * DV / 16 % 256 == 0 || tid + i * 256 < BJ * DV / 16) ? tid + i * 256 : 0;
       const int db = (s % (DV / 2)) * 2, jb = (s / (DV / 2)) * 8;
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) rv[i][jj] = *(const u16x2*)(Vb + offV_k(KEY(j0 + jb + jj)) + offV_col(db));
+      for (int jj = 0; jj < 8; ++jj) {
+        rv[i][jj] = *(const u16x2*)(Vb + offV_k(KEY(j0 + jb + jj)) + offV_col(db));
+        if (SK % BJ != 0 && j0 + jb + jj >= SK) rv[i][jj] = 0;
+      }
     }
 #endif
   };

@@ -56,6 +56,26 @@ def test_attention_masks_of_any_row_length(args, kw):
     assert len(_attention_blocks(s)) == 1, s.plan.describe()
 
 
+@pytest.mark.parametrize("SK,kt_stored", [(33, False), (130, False), (72, True), (72, False)])
+def test_attention_infinite_value_of_the_last_key(SK, kt_stored):
+    """An infinite value behind a probability above zero is an infinite result: the keys that fill up the last tile add nothing."""
+    from oracle.interp import run_graph
+    from paper_2108_13342_amd import api
+
+    spec = U.attention_block(1, 2, 40, SK, 64, dtype="bf16", mask=None, kt_stored=kt_stored)
+    v = np.array(spec.tensors["v"].data, dtype=np.float64)
+    v[0, 1, SK - 1, 3], v[0, 0, SK - 1, 7] = np.inf, -np.inf
+    spec.tensors["v"].data = v
+    s = api.Session(spec, attention=1)
+    assert len(_attention_blocks(s)) == 1
+    s.run()
+    got = list(s.result().values())[0]
+    want = list(run_graph(spec).values())[0]
+    assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want)) and not np.isnan(got).any()
+    finite = np.isfinite(want)
+    assert np.isinf(want).any() and rel_err(got[finite], want[finite]) <= TOL["bf16"]
+
+
 def test_attention_keys_stored_transposed_need_vectors():
     """K handed over as its transpose is read along the keys: a number that is no multiple of 8 stays three blocks."""
     s, _ = check_against_oracle(U.attention_block(1, 2, 33, 33, 64), attention=1)

@@ -1082,6 +1082,7 @@ Lowered lower_block(const Graph& g, const Block& b, const LowerOpts& o) {
         ok = ok && X.kind == DNNF_INTERMEDIATE && X.producer >= 0 && !X.weight_only && X.perm.empty() && X.dtype == R.dtype && X.bytes() == part_bytes &&
              g.ops[X.producer].info->cls != OC_RESHAPE && g.ops[X.producer].info->cls != OC_CONCAT;
         for (auto& pr : parts) ok = ok && pr.first != t;
+        ok = ok && start % 16 == 0;          // (readers load 16-byte vectors, and such vectors straight into LDS)
         parts.push_back({t, start});
         start += part_bytes;
       }

@@ -63,3 +63,20 @@ def test_depthwise_kernel_by_estimate(args, dtype, kernel):
     b.mark_output(configs._un(b, "Relu", configs._conv(b, x, b.weight("w", (C, 1, K, K), zeros((C, 1, K, K))), None, stride, K // 2, C)))
     names = [n for n, _ in _sources(b.finish(), layout=1) if n.startswith("dw_")]
     assert len(names) == 1 and names[0].startswith(kernel), names
+
+
+@pytest.mark.parametrize("rows,inside", [((3, 5), False), ((8, 5), True), ((4, 4), False)])
+def test_concat_operands_stay_inside_the_result_only_on_16_byte_boundaries(rows, inside):
+    b = GraphBuilder("cat", "f16")
+    zeros = lambda shape: np.zeros(shape, dtype=np.float32)
+    w = b.weight("w", (16, 7), zeros((16, 7)))
+    parts = [configs._un(b, "Relu", configs._matmul(b, b.input(f"x{i}", (r, 16), zeros((r, 16))), w)) for i, r in enumerate(rows)]
+    for p in parts:
+        b.mark_output(configs._un(b, "Sigmoid", configs._matmul(b, p, b.weight("v" + p, (7, 9), zeros((7, 9))))))
+    y = b.op("Concat", parts, (sum(rows), 7), {"axis": 0})
+    b.mark_output(y)
+    spec = b.finish()
+    g, _ = api.graph_from_spec(spec)
+    g.rewrite()
+    names = [d["kernel_name"] for d in api.Plan(g, [1] * len(spec.weights())).describe() if "Concat" in d["ops"]]
+    assert len(names) == 1 and ("alias_concat" in names[0]) == inside, names

@@ -910,16 +910,7 @@ Lowered lower_conv(LowerCtx& c) {
         k << "  const idx_t a" << xh << " = min(max(h_, 0), " << H - 1 << "), a" << xw << " = min(max(w_, 0), " << Wd - 1 << ");\n";
       }
       k << c.decl_parts(xatoms, "  ");
-      const ENode& xe = c.nodes[xnode];
-      if (xe.kind == ENode::LOAD && !xe.is_int && xe.addr.indirect.empty() && g.tensors[xe.tensor].dtype == X.dtype) {
-        // a stored element goes as it is: through float and back, bf16 values were waited for one by one (residual block
-        // 16x128x70x66 in bf16 228 us, 105 now; decoder half of a U-Net 8x256x16x16 in the declared order 425, 191)
-        k << "  const elem_t o = p" << pslot.at(xe.tensor) << "[" << c.addr_expr(xe.addr) << "];\n";
-      } else {
-        std::set<int> done;
-        c.emit_values(k, {xnode}, done, pslot, "  ");
-        k << "  elem_t o; cvt_out(&o, " << c.vname(xnode) << ");\n";
-      }
+      c.emit_element(k, xnode, X.dtype, pslot, "  ");
       k << (branch ? "  return o;\n}\n" : "  return in_ ? o : (elem_t)0;\n}\n");
       k << "#define loadB_gather(Bb, kk, g) loadB_gather_impl(kk, g, KARGS_G)\n";
       if (direct) {

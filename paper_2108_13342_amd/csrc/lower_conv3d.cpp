@@ -169,15 +169,8 @@ Lowered lower_conv3d(LowerCtx& c) {
   k << "  if (a" << xd << " < 0 || a" << xd << " >= " << D << " || a" << xh << " < 0 || a" << xh << " >= " << H << " || a" << xw << " < 0 || a" << xw << " >= " << Wd
     << ") return (elem_t)0;\n";
   k << c.decl_parts(xatoms, "  ");
-  const ENode& xe = c.nodes[xnode];
-  if (xe.kind == ENode::LOAD && !xe.is_int && xe.addr.indirect.empty() && g.tensors[xe.tensor].dtype == X.dtype) {
-    // a stored element goes as it is: through float and back, bf16 values would be waited for one by one
-    k << "  return p" << pslot.at(xe.tensor) << "[" << c.addr_expr(xe.addr) << "];\n}\n";
-  } else {
-    std::set<int> done;
-    c.emit_values(k, {xnode}, done, pslot, "  ");
-    k << "  elem_t o; cvt_out(&o, " << c.vname(xnode) << "); return o;\n}\n";
-  }
+  c.emit_element(k, xnode, X.dtype, pslot, "  ");
+  k << "  return o;\n}\n";
   k << "#define loadB_gather(Bb, kk, g) loadB_gather_impl(kk, g, KARGS_G)\n";
   k << gemm_epilogue_source(c, {}, rows, cols, pslot, kparams, GN, bslot, dot ? 0 : GM);
   k << "#define KPARAMS " << kparams << "\n#define KARGS " << kargs << "\n";

@@ -115,6 +115,8 @@ struct LowerCtx {
                    const std::map<int, int>& pslot, const std::string& indent,
                    const std::map<int, std::string>* load_override = nullptr) const;
   std::string addr_expr(const Affine& a) const;
+  // the value of node n as an element of the template's storage type, in a variable `o`
+  void emit_element(std::ostringstream& os, int n, int dtype, const std::map<int, int>& pslot, const std::string& ind) const;
   std::string store_stmt(const Store& s, const std::map<int, int>& pslot, const std::string& off) const;
   std::string pred_expr(const std::vector<Pred>& p) const;
   std::string vname(int node) const { return "v" + std::to_string(node); }

@@ -213,12 +213,16 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // weight stored [K][N] a run of columns is a strip of every row (W_PF_STRIP lines of it); of one in another order the
   // lines are not told apart (W_PF_WHOLE).
   // In the direct-to-LDS loop every wavefront issues W_PF_N loads (lanes past its share touch the last line again): they are
-  // counted there.  The register-staged loop touches before it loads anything, through the compiler's builtin, which then
-  // knows of no load in flight at the loop's entry: behind the first tiles, as assembly, the waits it placed for their
-  // registers moved into the loop, in front of every tile's multiplications (bf16 4174x1763x216, A read element by element:
-  // 47 us, 61).
+  // counted there.  A register-staged loop whose operands come element by element touches before it loads anything
+  // (W_PF_FIRST), through the compiler's builtin, which then knows of no load in flight at the loop's entry: behind the
+  // first tiles, as assembly, the waits it placed for their registers moved into the loop, in front of every tile's
+  // multiplications (bf16 4174x1763x216 47 us, 61; 3x3 f16 in the declared order 2x64x40x40 8.4, 9.6).  One that loads
+  // vectors touches behind its first tiles (f32 1100x2048x1100 83.9, 82.9; 3x3 f32 channels-last 3x64x28x28 6.7, 6.3).
   // Lines of a [K][N] weight, us in a row of products (all, a run of lines as of [N][K], the strip): bf16 512x1001x3072 36.1,
   // 42.1, 29.7; 33x4100x1000 68.5, 67.1, 53.4; f32 10x1038x1401 41.4, 41.4, 24.6; 33x2985x178 78.7, 98.3, 67.3.
+#if !defined(DMA) && (A_MODE == 2 || B_MODE == 2 || B_MODE == 3 || defined(W_PF_STRIP) || defined(W_PF_WHOLE))
+#define W_PF_FIRST 1
+#endif
   auto touch_weights = [&]() {
     const idx_t nb = tiles_m * tiles_n, x = blockIdx.x % 8, nx = nb / 8 + (x < nb % 8 ? 1 : 0);
     const idx_t t0 = bid - blockIdx.x / 8, t1 = t0 + nx - 1;
@@ -243,12 +247,16 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
     const idx_t l0 = (idx_t)((long long)lo * GK * ELEM_BYTES / 128), l1 = to_end ? (idx_t)W_PREFETCH_LINES : (idx_t)((long long)hi * GK * ELEM_BYTES / 128);
 #endif
     const idx_t per = (l1 - l0 + nx - 1) / nx, first = l0 + (blockIdx.x / 8) * per, end = first + per < l1 ? first + per : l1;
-#ifdef DMA
+#ifndef W_PF_FIRST
     const u32 spare = lds_address(smem + SMEM_MAIN + (RA ? 4 * BM : 0));
 #pragma unroll
     for (int i = 0; i < W_PF_N; ++i) {
       const idx_t line = first + tid + i * NT;
+#ifdef DMA
       load_to_lds4((const char*)W_PREFETCH_PTR + (long long)(line < end ? line : l1 - 1) * 128, spare);
+#else
+      if (line < end) load_to_lds4((const char*)W_PREFETCH_PTR + (long long)line * 128, spare);
+#endif
     }
 #else
     typedef __attribute__((address_space(1))) const void* gptr_t;
@@ -268,7 +276,7 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
 #define W_PF_N 0
   auto touch_weights = [&]() {};
 #endif
-#ifndef DMA
+#ifdef W_PF_FIRST
   touch_weights();
 #endif
 
@@ -812,6 +820,9 @@ extern "C" __global__ __launch_bounds__(NT) void KNAME(KPARAMS) {
   // tiles are loaded ahead, so the latency of a tile's global loads overlaps PF - 1 tiles of MFMA work.
 #pragma unroll
   for (int s = 0; s < PF; ++s) gload(s, (idx_t)s * BK);
+#ifndef W_PF_FIRST
+  touch_weights();
+#endif
   lstore(0, 0, 0);
   __syncthreads();
   for (int kt0 = 0; kt0 < nk; kt0 += PF) {
@@ -1647,7 +1658,10 @@ Lowered lower_gemm(LowerCtx& c, LowerCtx* norm, int norm_in, bool norm_in_stored
         return true;
       };
       const TouchOrder order = dense(katoms, cols) ? TOUCH_COLS : !DMA && dense(cols, katoms) ? TOUCH_STRIP : TOUCH_WHOLE;
-      k << weight_touch_macros(wbytes / 128, 1, order, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K, eb, 64 * WAVES_M * WAVES_N * WAVES_K);
+      // (a strip's lines lie apart, and where K is short few round trips are saved for them: bf16 25x879x163 11.2 us, 10.2 without
+      // touches; 25x870x763 12.1, 11.7; 1x621x259 7.5, 6.7; but f32 10x1038x1401 24.6, 37.8; bf16 512x1001x3072 29.7, 32.2)
+      if (order != TOUCH_STRIP || K >= 1000)
+        k << weight_touch_macros(wbytes / 128, 1, order, (GM + BM - 1) / BM, (GN + BN - 1) / BN, BM, BN, GM, GN, K, eb, 64 * WAVES_M * WAVES_N * WAVES_K);
     }
   }
   if (TA.dtype == DNNF_F16) k << "typedef f16x8 frag_t;\n#define MFMA __builtin_amdgcn_mfma_f32_32x32x16_f16\n";

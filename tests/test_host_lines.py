@@ -35,7 +35,7 @@ def test_squeeze_excite_weights_up_front(args, kw, early):
 
 @pytest.mark.parametrize("M,K,N,dtype,rewrite,strip", [
     (64, 1024, 1024, "bf16", True, 0),                                  # stored [N][K] after rewriting
-    (64, 132, 1024, "bf16", True, 3),                                   # K no multiple of a vector: stays [K][N]; an XCD's two tiles of 64
+    (64, 1004, 1024, "bf16", True, 3),                                  # K no multiple of a vector: stays [K][N]; an XCD's four tiles of 32
     (64, 1024, 1024, "bf16", False, 3),                                 # not rewritten; four tiles of 32
     (64, 1001, 1024, "f32", True, 5),
     (2000, 1001, 300, "f32", True, 11),                                 # an XCD's tiles cover all columns
@@ -43,7 +43,7 @@ def test_squeeze_excite_weights_up_front(args, kw, early):
 def test_weight_touches_cover_what_the_tiles_read(M, K, N, dtype, rewrite, strip):
     """A run of columns is a run of memory lines only where the weight's rows of K lie one behind the other."""
     src = _sources(U.gemm_block(M, K, N, dtype), rewrite)[0][1]
-    assert "#define W_PREFETCH_LINES" in src and "#define W_PF_WHOLE" not in src
+    assert "#define W_PREFETCH_LINES" in src and "#define W_PF_WHOLE" not in src and "#define W_PREFETCH_LINES" not in _sources(U.gemm_block(M, 900, N, dtype), False)[0][1]
     assert (f"#define W_PF_STRIP {strip}\n" in src) if strip else ("#define W_PF_STRIP" not in src)
 
 

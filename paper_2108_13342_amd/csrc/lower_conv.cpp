@@ -815,7 +815,12 @@ Lowered lower_conv(LowerCtx& c) {
         for (auto& d : dma_forms()) {
           if (GM <= 64 && d.BM > 64) continue;
           const double t = dma_time(d, (double)nblocks(d.BM, d.BN), nk);
-          if (n32 > 704 && t < best) { best = t; dma_pick = tiles.size(); }
+          // Channels that are no multiple of 8 are stored one value at a time, which the model's time of a workgroup does not
+          // hold: with few K tiles that store is much of a 128x128 tile, and smaller tiles run it beside another's loop.  60 such
+          // convolutions, us with 128x128 and without: 10x496x21x21 -> 527 1x1 13.4, 12.2; 1x64x107x107 -> 474 3x3 22.5, 17.0;
+          // 4x136x79x79 -> 115 1x1 10.2, 7.8; 2x16x67x67 -> 370 3x3 11.3, 8.4; the other way 50x80x24x24 -> 234 3x3 18.2, 21.2.
+          const bool long_store = GM % VEC && d.BM * d.BN >= 128 * 128 && nk < 20;
+          if (n32 > 704 && t < best && !long_store) { best = t; dma_pick = tiles.size(); }
           tiles.push_back({d.BM, d.BN, d.WM, d.WN, 1, 64, false, d.NBUF});
         }
       }

@@ -56,3 +56,14 @@ def test_environment_does_not_reach_convolution_tiles(monkeypatch):
     plain = _kernels(spec, layout=1)
     monkeypatch.setenv("DNNF_CONV_TILE", "32,32,64,0,0,0,2")
     assert _kernels(spec, layout=1) == plain
+
+
+@pytest.mark.parametrize("args,large", [((1, 64, 107, 107, 474, 3), False), ((1, 64, 107, 107, 480, 3), True),
+                                        ((10, 496, 21, 21, 527, 1), False), ((10, 496, 21, 21, 528, 1), True),
+                                        ((4, 168, 64, 64, 474, 3), True)])       # 24 K tiles: the store is little of it
+def test_tiles_of_results_stored_one_at_a_time(args, large):
+    """Channels that are no multiple of 8 and few K tiles: no 128x128 tile, whose store alone would take as long as its loop."""
+    names = _kernels(U.conv_pair_block(*args), layout=1)
+    name = next(n for n in names if n.startswith("igemm_") and "_dma" in n)
+    bm, bn = map(int, name.split("_")[1].split("x")[:2])
+    assert (bm * bn >= 128 * 128) == large, names

@@ -17,6 +17,9 @@
  *     frees device memory: tensors and the workspace belong to the caller.
  *   - Tensors are dense, row-major, in the layout the operator definitions use
  *     (NCHW for Conv, [..., M, K] x [..., K, N] for MatMul).
+ *   - Device buffers of inputs, outputs and weights start on 16-byte boundaries
+ *     (the allocators of HIP and of torch give more): kernels read and write
+ *     their tensors in 16-byte vectors.
  *   - Handles are created and destroyed by the library; all graph structure
  *     passed in is copied.
  */

@@ -1031,7 +1031,12 @@ const char* gemm_kernel_zeros() { return "static __device__ __attribute__((align
 // takes 48 KB of LDS (three workgroups on a compute unit), 128x128 on two 64 KB (two) and on three 96 KB (one).  Fitted to 35
 // products in bf16 (M 256 .. 8192, K 128 .. 3072, N 128 .. 3072, weights from beyond the L2 caches) on every form, 5 to 11 %
 // rms each; the form it names is 3 % slower than the best of them on average, where a model of matrix and LDS cycles was 16 %
-// slower, and up to 1.7 times (2048x1536x384 15.1 against 8.9).
+// slower, and up to 1.7 times (2048x1536x384 15.1 against 8.9).  Outside the fit: K of 64 to 192, 66 products, three of them 7 to
+// 14 % slower than the cycle model's form (945x64x282 batch 4 4.2 against 3.7) and none beyond that; 105 convolutions, which
+// read their operands alike and whose tiles it names as well, see there.  Not in the list, since the tuner found no product
+// for them: 256x256 on sixteen wavefronts and 128x128 on four, us beside the eight-wavefront form: 4096x768x50257 400, 479
+// (395); 8192x4096x4096 240, 278 (228); 4096x4096x4096 122, 142 (116); 16384x1024x4096 150, 161 (141); ten layer products
+// of 512 to 4096 rows 7 to 12 % slower at best.
 const std::vector<DmaForm>& dma_forms() {
   static const std::vector<DmaForm> forms = {
       {64, 64, 2, 2, 2, 1.81, 0.352, 0.225, 0.81},  {64, 64, 2, 2, 3, 1.53, 0.260, 0.214, 1.13},   {64, 64, 2, 2, 4, 1.69, 0.255, 0.210, 0.98},

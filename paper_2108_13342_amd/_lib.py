@@ -76,6 +76,15 @@ def lib():
             raise RuntimeError(
                 f"{LIB_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`. "
                 "There is no CPU fallback for the fused-block executor.")
+        # The library compiles with whichever hipRTC the process holds, and torch brings one of its own, of another version
+        # than the system's.  Runs have torch loaded; loaded here first, it is the compiler of host-only processes too - the
+        # ones that fill kernel_cache/ - and a kernel's code does not depend on which process came first.  The streaming
+        # attention block at 48 x 1024 x 1024 x 64: 47.1 us compiled by torch's, 53.7 by the system's; the decoder's
+        # vocabulary product 373 and 381; the other kernels of the benchmark graphs the same within 1 %.
+        try:
+            import torch  # noqa: F401
+        except ImportError:
+            pass
         l = C.CDLL(LIB_PATH)
         for name, (res, args) in EXPORTS.items():
             fn = getattr(l, name)   # AttributeError if a declared symbol is not exported

@@ -110,14 +110,29 @@ def _prewarm_one(job):
         return f"prewarm {name} {opts}: {e}"
 
 
+def _compiler() -> str:
+    """The compiler whose code objects kernel_cache/ holds: torch's, which is loaded in front of the library."""
+    try:
+        import torch
+    except ImportError:
+        return ROCM
+    return f"torch {torch.__version__}"
+
+
 def prewarm(verbose: bool = False, workers: int = 6) -> int:
     """Generate and compile the kernels of the benchmark graphs (fused and unfused plans) into kernel_cache/.
     Kernels are keyed by a hash of their source: code objects that are still current are kept, the ones earlier
-    generator versions left behind are dropped at the end."""
+    generator versions left behind are dropped at the end, and those of another compiler at the start."""
     import multiprocessing as mp
     import time
 
     os.makedirs(CACHE, exist_ok=True)
+    stamp = os.path.join(CACHE, "compiler.tsv")
+    if not os.path.exists(stamp) or open(stamp).read() != _compiler():
+        for f in glob.glob(os.path.join(CACHE, "*.hsaco")):
+            os.remove(f)
+        with open(stamp, "w") as f:
+            f.write(_compiler())
     t0 = time.time() - 2.0
     os.environ["DNNF_CACHE_TOUCH"] = "1"
     try:
